@@ -423,8 +423,8 @@ im_status im_dual_update(im_pool* pool, double eta, double lambda_max, double* l
  * it use the new shapes; no result depends on them; not stream-ordered):
  *   route_blocks  grid of the persistent route kernels: -1 one block per
  *                 compute unit (the default), n > 0 at most n blocks sharing
- *                 the tick's row tiles, 0 the kernels that launch one wave
- *                 per row tile instead
+ *                 the tick's row tiles, 0 the kernels that launch one block
+ *                 per group of rows instead
  *   sched_waves   envs (one wave each) per workgroup of the schedule step:
  *                 1, 2 or 4 (the default); 0 keeps the current value
  * IM_EINVAL for other values. */

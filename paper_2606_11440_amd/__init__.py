@@ -107,7 +107,7 @@ class Pool:
 
     def set_launch(self, route_blocks, sched_waves=0):
         """Launch shapes (results do not depend on them): route_blocks -1
-        default, n > 0 persistent grid of n blocks, 0 one wave per tile;
+        default, n > 0 persistent grid of n blocks, 0 a block per group of rows;
         sched_waves 1, 2 or 4 envs per schedule workgroup (0: keep)."""
         im_set_launch(self.h, route_blocks, sched_waves)
 

@@ -125,6 +125,7 @@ struct RouteArgs {
   float* logits;
   int32_t* err;
   int32_t persistent_blocks;          // grid of the persistent kernels (0: never use them)
+  int32_t cus;                        // compute units of the device
   // RL-rollout outputs (im_route_sample)
   int32_t rl;                         // 1: log-prob, entropy, value; sampled or greedy action
   int32_t greedy;                     // with rl: 1 = masked argmax, 0 = Gumbel-max sample
@@ -191,6 +192,9 @@ hipError_t launch_dual_update(const int64_t* cnt, int64_t n_em, const int64_t* e
                               double* lambda, hipStream_t s);
 bool route_supported(int dtype, int hidden, int n_layers, int out_tiles);
 bool dual_supported(int embed_dim, int out_rows);
+// bf16 MLP policies of any shape, features split over a block's waves (route_split.hip).
+bool split_supported(int hidden);
+hipError_t launch_split(const RouteArgs& a, int hidden, int n_layers, int out_tiles, hipStream_t s);
 // Role projections of the dual-pathway executor: out[r][tile][g][16] =
 // b_sem + W_sem[:, E_d:] e_r in fp32 for every role r (bf16 inputs).
 //   w_role [128 x E_d] bf16 bits, roles [n_roles x E_d] bf16 bits, b_sem [128]

@@ -571,6 +571,7 @@ static im::RouteArgs route_args(im_pool* p, const im_arrivals* arr, int32_t* act
   a.logits = logits;
   a.err = p->err;
   a.persistent_blocks = p->route_blocks < 0 ? p->cu_count : p->route_blocks;
+  a.cus = p->cu_count;
   a.net = p->d.net;
   if (p->d.net == IM_NET_DUAL) {
     a.role = arr->role;
