@@ -32,14 +32,11 @@ constexpr int kRpmRing = 64;     // bytes per (env, model) of the per-tick dispa
 // Per-env snapshot row read by the route step, written by the schedule step
 // (and by snapshot_kernel after host-side state changes): the 4M load-stat
 // features in stat-major order as fp32 (each one product of an integer and a
-// reciprocal rounded once to fp32), then one validity byte per model (enabled,
-// c_m > 0 and queue below capacity), padded so 8 consecutive floats can always
-// be read from any feature index < 4M.
-__host__ __device__ inline int snap_stride(int M) {
-  const int n = 4 * M + (M + 3) / 4 + 8;
-  return (n + 7) & ~7;
-}
-__host__ __device__ inline int snap_valid_offset(int M) { return 4 * M; }   // in floats
+// reciprocal rounded once to fp32), then the 64-bit mask of the valid actions
+// (bit a: action a's model is enabled, c_m > 0 and its queue below capacity),
+// padded so 8 consecutive floats can always be read from any feature index < 4M.
+__host__ __device__ inline int snap_stride(int M) { return (4 * M + 8 + 7) & ~7; }
+__host__ __device__ inline int snap_mask_offset(int M) { return 4 * M; }   // in floats (16-byte aligned)
 
 // Counter slots per (env, model), int64. C_COST_Q16 sums floor(2^16 latency /
 // budget) over completions (the cost of Eq. 2, for the dual update of Eq. 7).

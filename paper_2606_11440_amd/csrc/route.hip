@@ -39,87 +39,77 @@ namespace {
 // Same rules as the 32-row epilogue: lowest action on exact ties, Philox block
 // (id, env, action / 4) per four consecutive actions.
 template <int AT>
-__device__ __forceinline__ void epilogue16(const RouteArgs& a, const RowCtx& c, const f32x4 (&acc)[AT], int q) {
-  float best = 0.f;
-  int ba = -1;
+__device__ __forceinline__ void epilogue16(const RowCtx& c, const f32x4 (&acc)[AT], int q) {
+  const KernArgs a = late_args();
+  // bit 16 T + r: action 16 T + 4 q + r is masked
+  const uint64_t inv = (uint64_t)((int64_t)~c.amask >> (4 * q));
+  const uint32_t mw[2] = {(uint32_t)inv, (uint32_t)(inv >> 32)};
+  float zm[AT][4];
+  float best = __uint_as_float(0xffffffffu);
 #pragma unroll
   for (int T = 0; T < AT; ++T) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int act = 16 * T + 4 * q + r;
-      const float z = acc[T][r];
-      if (act < a.A && ((c.amask >> act) & 1ull)) {
-        if (ba < 0 || z > best) { best = z; ba = act; }
-      }
-    }
+    for (int r = 0; r < 4; ++r) zm[T][r] = mask_logit(acc[T][r], bit_ones(mw[T >> 1], 16 * (T & 1) + r));
+    best = max3(best, zm[T][0], zm[T][1]);
+    best = max3(best, zm[T][2], zm[T][3]);
   }
+  int32_t ba = 127;
 #pragma unroll
   for (int off = 16; off <= 32; off *= 2) {
-    const float ob = __shfl_xor(best, off, 64);
-    const int oa = __shfl_xor(ba, off, 64);
-    if (oa >= 0 && (ba < 0 || ob > best || (ob == best && oa < ba))) { best = ob; ba = oa; }
+    const float o = __shfl_xor(best, off, 64);
+    best = max3(best, o, o);
   }
-  if (a.rl) {
-    const bool sample = a.greedy == 0;
+#pragma unroll
+  for (int T = AT - 1; T >= 0; --T)
+#pragma unroll
+    for (int r = 3; r >= 0; --r) ba = zm[T][r] == best ? 16 * T + r : ba;
+  ba += 4 * q;
+#pragma unroll
+  for (int off = 16; off <= 32; off *= 2) ba = min(ba, __shfl_xor(ba, off, 64));
+  // -1 when no action is valid; the first valid one when every valid logit is NaN
+  if (ba >= 64) ba = __ffsll((unsigned long long)c.amask) - 1;
+  if (a->rl) {
+    const bool sample = a->greedy == 0;
     uint32_t id = 0;
-    if (sample) {
-      id = request_id(a, c);
-    }
-    float sm = 0.f, sz = 0.f, val = 0.f, bs = 0.f, bz = 0.f;
-    int bsa = -1;
+    if (sample) id = request_id(a, c);
+    RlSums s;
+    float val = 0.f;
 #pragma unroll
     for (int T = 0; T < AT; ++T) {
-      const int a0 = 16 * T + 4 * q;   // this lane's 4 consecutive actions: one Philox block
-      uint4 w = make_uint4(0, 0, 0, 0);
-      if (sample && a0 < a.A) w = philox10(make_uint4(id, (uint32_t)c.e, (uint32_t)(a0 >> 2), 0u), a.seed_lo, a.seed_hi);
-      const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int act = a0 + i;
-        const float z = acc[T][i];
-        if (act == a.A) val = z;
-        if (act < a.A && ((c.amask >> act) & 1ull)) {
-          const float ex = __expf(z - best);
-          sm += ex;
-          sz += ex * z;
-          const float sc = sample ? __fdividef(ex, expo_of(wv[i])) : z;
-          if (bsa < 0 || sc > bs) { bs = sc; bsa = act; bz = z; }   // actions ascend: ties keep the lowest
+      const float z[4] = {acc[T][0], acc[T][1], acc[T][2], acc[T][3]};
+      const uint32_t mb = mw[T >> 1] >> (16 * (T & 1));
+      if (16 * T < a->A) {   // uniform
+        if (sample) {
+          const uint4 w = philox10(make_uint4(id, (uint32_t)c.e, (uint32_t)(4 * T + q), 0u), a->seed_lo, a->seed_hi);
+          rl_block<true>(s, z, mb, best, 16 * T + 4 * q, w);
+        } else {
+          rl_block<false>(s, z, mb, best, 16 * T + 4 * q, make_uint4(0, 0, 0, 0));
         }
+      }
+      if (a->value && (a->A >> 4) == T) {   // uniform: the tile of row A
+        const int i = a->A & 3;
+        const float v = i == 0 ? z[0] : (i == 1 ? z[1] : (i == 2 ? z[2] : z[3]));
+        val = ((a->A >> 2) & 3) == q ? v : 0.f;
       }
     }
 #pragma unroll
     for (int off = 16; off <= 32; off *= 2) {
-      sm += __shfl_xor(sm, off, 64);
-      sz += __shfl_xor(sz, off, 64);
+      rl_join(s, __shfl_xor(s.s, off, 64), __shfl_xor(s.sz, off, 64), __shfl_xor(s.bs, off, 64),
+              __shfl_xor(s.bz, off, 64), __shfl_xor(s.ba, off, 64));
       val += __shfl_xor(val, off, 64);             // one lane of the row holds row A
-      const float obs = __shfl_xor(bs, off, 64), obz = __shfl_xor(bz, off, 64);
-      const int obsa = __shfl_xor(bsa, off, 64);
-      if (obsa >= 0 && (bsa < 0 || obs > bs || (obs == bs && obsa < bsa))) { bs = obs; bsa = obsa; bz = obz; }
     }
-    if (c.live && q == 0) {
-      const bool any = ba >= 0 && !c.bad;
-      const float lse = any ? best + __logf(sm) : 0.f;
-      a.actions[c.r] = any ? bsa : -1;
-      if (c.bad) atomicOr(a.err, c.bad);
-      if (a.logp) a.logp[c.r] = any ? bz - lse : 0.f;
-      if (a.entropy) a.entropy[c.r] = any ? lse - sz / sm : 0.f;
-      if (a.value) a.value[c.r] = c.bad ? 0.f : val;
-    }
+    if (c.live && q == 0) rl_store(a, c, s, best, ba, val);
   } else if (c.live && q == 0) {
-    a.actions[c.r] = c.bad ? -1 : ba;
-    if (c.bad) atomicOr(a.err, c.bad);
+    a->actions[c.r] = c.bad ? -1 : ba;
+    if (c.bad) atomicOr(a->err, c.bad);
   }
   if (!c.live) return;
-  if (a.logits) {
-    float* out = a.logits + (size_t)c.r * a.A;
+  if (a->logits) {
+    float* out = a->logits + (size_t)c.r * a->A;
 #pragma unroll
-    for (int T = 0; T < AT; ++T) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int act = 16 * T + 4 * q + r;
-        if (act < a.A) out[act] = c.bad ? 0.f : acc[T][r];
-      }
-    }
+    for (int T = 0; T < AT; ++T)
+      store_logits(a, out, 16 * T + 4 * q, c.bad ? 0.f : acc[T][0], c.bad ? 0.f : acc[T][1], c.bad ? 0.f : acc[T][2],
+                   c.bad ? 0.f : acc[T][3]);
   }
 }
 
@@ -267,7 +257,7 @@ __global__ __launch_bounds__(256) void route_f32(RouteArgs a_in) {
       for (int r = 0; r < 4; ++r) h2[T][r] = relu(h2[T][r]);
     layer16<AT, KGH, 2>((const f32x4*)a.W[2], a.bias[2], h2, lane, q, out);
   }
-  epilogue16<AT>(a, c, out, q);
+  epilogue16<AT>(c, out, q);
 }
 
 // TQ output tiles [To0, To0 + TQ) of a layer over its hidden input, read from
@@ -403,7 +393,7 @@ __global__ __launch_bounds__(256) void route_f32s(RouteArgs a_in) {
   if (wave != 0) return;
   f32x4 out[AT];
   layer16_lds<AT, KGH, 2>((const f32x4*)a.W[NL - 1], a.bias[NL - 1], hs, 0, lane, q, out);
-  epilogue16<AT>(a, c, out, q);
+  epilogue16<AT>(c, out, q);
 }
 
 // ---------------------------------------------------------------------------
@@ -501,19 +491,11 @@ __global__ __launch_bounds__(NW * 64, 1) void route_bf16_lds(RouteArgs a_in) {
 #pragma unroll
     for (int j = 0; j < NR; ++j) rows[j] = r0 + 32 * j + n;
     find_envs_in<NR>(a, f.w, r0, rlast, rows, envs);
-    ValidRaw vr[NR];
 #pragma unroll
-    for (int j = 0; j < NR; ++j) {
-      c[j] = row_ctx_from(a, rows[j], envs[j], f.q[j], f.bud[j]);
-      vr[j] = load_valid(a, envs[j]);
-    }
+    for (int j = 0; j < NR; ++j) c[j] = row_ctx_from(a, rows[j], envs[j], f.q[j], f.bud[j]);
     TailRaw<ED, KB1> raw[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) gather_issue<ED, KB1>(a, c[j], gg, x[j], raw[j]);
-    // the masks wait only for their own words: the embedding and snapshot
-    // loads issued after them stay in flight
-#pragma unroll
-    for (int j = 0; j < NR; ++j) c[j].amask = mask_of(a, vr[j]);
 #pragma unroll
     for (int j = 0; j < NR; ++j) gather_finish<ED, KB1>(a, c[j], gg, x[j], raw[j]);
   };
@@ -657,7 +639,7 @@ __global__ __launch_bounds__(NW * 64, 1) void route_bf16_lds(RouteArgs a_in) {
     }
     const int32_t un = u + NW;
 #pragma unroll
-    for (int j = 0; j < NR; ++j) epilogue<AT, RL>(a, c[j], o[j], nullptr, gg);
+    for (int j = 0; j < NR; ++j) epilogue<AT, RL>(c[j], o[j], gg);
     if (un >= ur.end) break;
     u = un;
     if constexpr (PIPE) setup(u, first_loads(u), c, x, gg);
@@ -774,11 +756,9 @@ __global__ __launch_bounds__(NW * 64, 1) void route_bf16_stream(RouteArgs a_in) 
     u32x4 x[KB1];
     if (act) {
       find_envs<1>(a, r0, rl, rsel, envs);
-      ValidRaw vr;
-      c = row_setup_env_raw(a, rows[0], envs[0], vr);
+      c = row_setup_env(a, rows[0], envs[0]);
       TailRaw<ED, KB1> raw;
       gather_issue<ED, KB1>(a, c, gg, x, raw);
-      c.amask = mask_of(a, vr);
       gather_finish<ED, KB1>(a, c, gg, x, raw);
     }
     if (!act) {
@@ -856,7 +836,7 @@ __global__ __launch_bounds__(NW * 64, 1) void route_bf16_stream(RouteArgs a_in) 
         }
       }
     }
-    epilogue<AT, RL>(a, c, z, nullptr, gg);
+    epilogue<AT, RL>(c, z, gg);
   }
   __builtin_amdgcn_s_waitcnt(0);   // the prefetched first stage of a step that does not exist
 }
@@ -987,10 +967,9 @@ __global__ __launch_bounds__(NW * 64, 1) void route_dual_bf16(RouteArgs a_in) {
     find_envs<NR>(a, r0, rlast, rows, envs);
     RowCtx c[NR];
     int32_t role[NR];
-    ValidRaw vr[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
-      c[j] = row_setup_env_raw(a, rows[j], envs[j], vr[j]);
+      c[j] = row_setup_env(a, rows[j], envs[j]);
       const int32_t ro = a.role[c[j].live ? rows[j] : a.n_total - 1];
       const bool bad_r = ro < 0 || ro >= a.n_roles;
       if (bad_r) c[j].bad |= IM_ERR_ROLE;
@@ -1006,8 +985,6 @@ __global__ __launch_bounds__(NW * 64, 1) void route_dual_bf16(RouteArgs a_in) {
 #pragma unroll
       for (int j = 0; j < NR; ++j) load_group<ED>(a, c[j], G, gg, x[G][j]);
     }
-#pragma unroll
-    for (int j = 0; j < NR; ++j) c[j].amask = mask_of(a, vr[j]);
     // ---- resource pathway, computed while the first embedding groups load ----
     u32x4 hr[NR][4];
 #pragma unroll
@@ -1110,7 +1087,7 @@ __global__ __launch_bounds__(NW * 64, 1) void route_dual_bf16(RouteArgs a_in) {
       for (int j = 0; j < NR; ++j) o[j][0] = mfma_bf16(w, hh[j][kb], o[j][0]);
     }
 #pragma unroll
-    for (int j = 0; j < NR; ++j) epilogue<1, RL>(a, c[j], o[j], nullptr, gg);
+    for (int j = 0; j < NR; ++j) epilogue<1, RL>(c[j], o[j], gg);
   }
 }
 

@@ -35,44 +35,11 @@ struct RowCtx {
   int32_t id = -1;  // the row's request id where the setup already read it (RL sampling)
 };
 
-// Valid actions of env e: bit a set when model a / K is valid in the env's
-// snapshot row (enabled, c_m > 0, queue below capacity).
-// The M <= 32 validity bytes start 16-byte aligned (byte 16 M of a row whose
-// stride is a multiple of 32 bytes) and the row's padding covers two 16-byte
-// words from there, so they arrive in one or two independent loads (a byte
-// loop would wait for each byte in turn).
-__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x) {
-  // bit i of the result: byte i of x is nonzero (OR-fold each byte into its
-  // low bit, then gather bits 0, 8, 16, 24 with one multiply: the shifted
-  // copies land on distinct bits, so no carries)
-  x |= x >> 4;
-  x |= x >> 2;
-  x |= x >> 1;
-  return ((x & 0x01010101u) * 0x00204081u) >> 21 & 0xfu;
+// Valid actions of env e: bit a set when action a's model is valid (enabled,
+// c_m > 0, queue below capacity), kept ready in the env's snapshot row.
+__device__ __forceinline__ uint64_t action_mask(const RouteArgs& a, int e) {
+  return *(const uint64_t*)(a.snap + (size_t)e * snap_stride(a.M) + snap_mask_offset(a.M));
 }
-__device__ __forceinline__ uint32_t valid_models16(const u32x4 w) {
-  return nonzero_bytes(w.x) | nonzero_bytes(w.y) << 4 | nonzero_bytes(w.z) << 8 | nonzero_bytes(w.w) << 12;
-}
-// The raw validity words of env e (both loaded for every M: the row's padding
-// covers them) and the action mask computed from them once they have arrived.
-struct ValidRaw {
-  u32x4 w0, w1;
-};
-__device__ __forceinline__ ValidRaw load_valid(const RouteArgs& a, int e) {
-  const u32x4* v = (const u32x4*)(a.snap + (size_t)e * snap_stride(a.M) + snap_valid_offset(a.M));
-  return {v[0], v[1]};
-}
-__device__ __forceinline__ uint64_t mask_of(const RouteArgs& a, const ValidRaw& v) {
-  uint32_t vm = valid_models16(v.w0);
-  if (a.M > 16) vm |= valid_models16(v.w1) << 16;
-  if (a.M < 32) vm &= (1u << a.M) - 1u;   // bytes past the M-th are padding
-  const uint64_t kmask = (a.K >= 64) ? ~0ull : ((1ull << a.K) - 1ull);
-  uint64_t am = 0;
-  for (int m = 0; m < a.M; ++m)
-    if ((vm >> m) & 1u) am |= kmask << (m * a.K);
-  return am;
-}
-__device__ __forceinline__ uint64_t action_mask(const RouteArgs& a, int e) { return mask_of(a, load_valid(a, e)); }
 
 // Env of rows r[] (per lane) for a wave whose rows lie in [rfirst, rlast]:
 // one coalesced load of a 64-entry window of offsets around an interpolated
@@ -154,7 +121,7 @@ __device__ __forceinline__ RowCtx row_ctx_from(const RouteArgs& a, int32_t r, in
   c.bad = (q < 0 || (int64_t)q >= a.Q) ? IM_ERR_QIDX : 0;
   c.q = c.bad ? 0 : q;
   c.budget = budget;
-  c.amask = 0;   // set by the caller from load_valid / mask_of
+  c.amask = action_mask(a, e);
   return c;
 }
 
@@ -169,23 +136,6 @@ __device__ __forceinline__ RowCtx row_setup_env(const RouteArgs& a, int32_t r, i
   c.q = c.bad ? 0 : q;
   c.budget = a.budget[rr];
   c.amask = action_mask(a, e);
-  return c;
-}
-
-// The same, leaving the action mask to the caller (load_valid's words are in
-// flight with the row's q_idx and budget).
-__device__ __forceinline__ RowCtx row_setup_env_raw(const RouteArgs& a, int32_t r, int32_t e, ValidRaw& vr) {
-  RowCtx c;
-  c.r = r;
-  c.live = r < a.n_total;
-  const int32_t rr = c.live ? r : a.n_total - 1;
-  c.e = e;
-  const int32_t q = a.q_idx[rr];
-  c.bad = (q < 0 || (int64_t)q >= a.Q) ? IM_ERR_QIDX : 0;
-  c.q = c.bad ? 0 : q;
-  c.budget = a.budget[rr];
-  vr = load_valid(a, e);
-  c.amask = 0;   // mask_of(a, vr) once the words have arrived
   return c;
 }
 
@@ -341,120 +291,209 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1) {
   return c;
 }
 
-// Exponential variate E = -ln U of a 32-bit word, U = (top 23 bits + 1/2)
-// 2^-23 (exact in fp32). Above U = 15/16, 1 - U = d is exact and -ln(1 - d)
-// is summed as d + d^2/2 + ... + d^7/7 (the rest is below 2^-24 d), so E keeps
-// its relative precision however close U is to 1.
-__device__ __forceinline__ float expo_of(uint32_t w) {
-  const uint32_t k = w >> 9;
-  const float u = ((float)k + 0.5f) * (1.0f / 8388608.0f);
-  const float d = ((float)(8388608u - k) - 0.5f) * (1.0f / 8388608.0f);
-  const float series =
-      d * (1.f + d * (0.5f + d * (1.f / 3.f + d * (0.25f + d * (0.2f + d * (1.f / 6.f + d * (1.f / 7.f)))))));
-  return d < 0.0625f ? series : -__logf(u);
+// The kernel's arguments (every route kernel takes one RouteArgs) where the
+// runtime put them, for code after a wave's matrix work: read there again with
+// scalar loads, they need not stay in scalar registers through it (the RL
+// kernels spilled them into vector registers). Chain pools: n_total is the bound.
+typedef const __attribute__((address_space(4))) RouteArgs* KernArgs;
+__device__ __forceinline__ KernArgs late_args() {
+  KernArgs k = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(k));
+  return k;
 }
 
-// Request id of a row: its env's next id plus the row's position in the env.
-__device__ __forceinline__ uint32_t request_id(const RouteArgs& a, const RowCtx& c) {
-  const int32_t rr = c.live ? c.r : a.n_total - 1;
-  return (uint32_t)(a.ms[(size_t)c.e * a.M].next_id + (rr - a.offsets[c.e]));
+// Request id of a row: its env's next id plus the row's position in the env
+// (a row past the last one: a number nobody uses).
+__device__ __forceinline__ uint32_t request_id(KernArgs a, const RowCtx& c) {
+  return (uint32_t)(a->ms[(size_t)c.e * a->M].next_id + (c.r - a->offsets[c.e]));
 }
 
-// RL-rollout outputs of one row from its logits (lane pair n, n + 32 holds
-// the row's actions 32 T + 8 (v / 4) + 4 g + v % 4): pi is the softmax of
-// the logits over the valid actions, shifted by their largest logit `zmax`
-// (action `amax`, -1 when none is valid); the action is the Gumbel-max draw
-// (or `amax` when greedy), its log-probability z_a - logsumexp, the entropy
-// logsumexp - sum pi z, and the value head's row A. The Gumbel-max draw
-// argmax z_a - ln(E_a), E_a = -ln U_a, is taken as the equivalent argmax of
-// exp(z_a - zmax) / E_a (one logarithm per action instead of two).
-template <int AT>
-__device__ __forceinline__ void rl_outputs(const RouteArgs& a, const RowCtx& c,
-                                           const f32x16 (&acc)[AT], int g, float zmax, int amax) {
-  const bool sample = a.greedy == 0;
-  uint32_t id = 0;
-  if (sample) {
-    id = c.id >= 0 ? (uint32_t)c.id : request_id(a, c);
-  }
-  float s = 0.f, sz = 0.f, val = 0.f, bs = 0.f, bz = 0.f;
-  int bsa = -1;
+// All ones where bit `bit` of `w` is set, else 0.
+__device__ __forceinline__ uint32_t bit_ones(uint32_t w, int bit) {
+  return (uint32_t)__builtin_amdgcn_sbfe((int)w, (uint32_t)bit, 1u);
+}
+// A logit, or a quiet NaN when `masked` is all ones; max3 and the compares
+// below pass over NaN operands, so a masked action needs no branch, and a valid
+// logit of -inf still differs from it.
+__device__ __forceinline__ float mask_logit(float z, uint32_t masked) {
+  return __uint_as_float(__float_as_uint(z) | masked);
+}
+// Largest operand that is not NaN (one instruction; fmaxf would first
+// canonicalise each operand).
+__device__ __forceinline__ float max3(float x, float y, float z) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+  return r;
+}
+__device__ __forceinline__ int32_t as_int(float x) { return __float_as_int(x); }
+
+// Softmax sums and the Gumbel-max draw over the actions a lane holds, four
+// consecutive ones (a Philox block) at a time. pi is the softmax of the logits
+// over the valid actions, shifted by their largest logit zmax. The draw argmax
+// z_a - ln(E_a), E_a = -ln U_a, is taken as the equivalent argmax of
+// exp(z_a - zmax) / -log2(U_a): one logarithm and one reciprocal per action,
+// and ln 2 scales every score alike. U_a = (top 23 bits + 1/2) 2^-23 is exact
+// in fp32, and the hardware log2 keeps its relative precision up to U = 1 - 2^-24
+// (largest error over all 2^23 values 1.2e-7). Branch-free: a masked action has
+// exp 0 and logit 0 in the sums, and a score of 0 never exceeds the best.
+struct RlSums {
+  float s = 0.f, sz = 0.f;    // sum of exp(z - zmax), of exp(z - zmax) z
+  float bs = 0.f, bz = 0.f;   // best score, its logit
+  int32_t ba = 127;           // its action
+};
+template <bool SAMPLE>
+__device__ __forceinline__ void rl_block(RlSums& r, const float (&z)[4], uint32_t masked_bits, float zmax,
+                                         int act0, uint4 w) {
+  const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-  for (int T = 0; T < AT; ++T) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int a0 = 32 * T + 8 * j + 4 * g;   // this lane's 4 consecutive actions: one Philox block
-      uint4 w = make_uint4(0, 0, 0, 0);
-      if (sample && a0 < a.A) w = philox10(make_uint4(id, (uint32_t)c.e, (uint32_t)(a0 >> 2), 0u), a.seed_lo, a.seed_hi);
-      const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int act = a0 + i;
-        const float z = acc[T][4 * j + i];
-        if (act == a.A) val = z;
-        if (act < a.A && ((c.amask >> act) & 1ull)) {
-          const float ex = __expf(z - zmax);
-          s += ex;
-          sz += ex * z;
-          const float sc = sample ? __fdividef(ex, expo_of(wv[i])) : z;
-          if (bsa < 0 || sc > bs) { bs = sc; bsa = act; bz = z; }   // actions ascend: ties keep the lowest
-        }
-      }
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t on = ~bit_ones(masked_bits, i);
+    const float ex = __uint_as_float(__float_as_uint(__builtin_amdgcn_exp2f((z[i] - zmax) * 1.44269504088896341f)) & on);
+    const float zv = __uint_as_float(__float_as_uint(z[i]) & on);
+    r.s += ex;
+    r.sz = fmaf(ex, zv, r.sz);
+    if constexpr (SAMPLE) {
+      const float u = fmaf((float)(wv[i] >> 9), 1.0f / 8388608.0f, 0.5f / 8388608.0f);
+      const float sc = ex * __builtin_amdgcn_rcpf(-__builtin_amdgcn_logf(u));
+      const bool take = sc > r.bs;   // actions ascend: ties keep the lowest
+      r.bs = take ? sc : r.bs;
+      r.bz = take ? zv : r.bz;
+      r.ba = take ? act0 + i : r.ba;
     }
   }
-  s += __shfl_xor(s, 32, 64);
-  sz += __shfl_xor(sz, 32, 64);
-  val += __shfl_xor(val, 32, 64);                  // one lane of the pair holds row A
-  const float obs = __shfl_xor(bs, 32, 64), obz = __shfl_xor(bz, 32, 64);
-  const int obsa = __shfl_xor(bsa, 32, 64);
-  if (obsa >= 0 && (bsa < 0 || obs > bs || (obs == bs && obsa < bsa))) { bs = obs; bsa = obsa; bz = obz; }
-  if (!c.live || g != 0) return;
-  const bool any = amax >= 0 && !c.bad;
-  const float lse = any ? zmax + __logf(s) : 0.f;
-  a.actions[c.r] = any ? bsa : -1;
-  if (c.bad) atomicOr(a.err, c.bad);
-  if (a.logp) a.logp[c.r] = any ? bz - lse : 0.f;
-  if (a.entropy) a.entropy[c.r] = any ? lse - sz / s : 0.f;
-  if (a.value) a.value[c.r] = c.bad ? 0.f : val;
+}
+// Adds the sums of another lane of the same row; the larger score wins, the
+// lower action on a tie.
+__device__ __forceinline__ void rl_join(RlSums& r, float s, float sz, float bs, float bz, int32_t ba) {
+  r.s += s;
+  r.sz += sz;
+  const bool take = bs > r.bs || (bs == r.bs && ba < r.ba);
+  r.bs = take ? bs : r.bs;
+  r.bz = take ? bz : r.bz;
+  r.ba = take ? ba : r.ba;
+}
+// The outputs of row c: any: some action is valid and the row's inputs are.
+__device__ __forceinline__ void rl_store(KernArgs a, const RowCtx& c, RlSums& r, float zmax, int32_t amax,
+                                         float val) {
+  const bool any = c.amask != 0 && !c.bad;
+  if (a->greedy) {
+    r.ba = amax;
+    r.bz = zmax;
+  } else if (r.ba >= 64) {
+    r.ba = __ffsll((unsigned long long)c.amask) - 1;   // no score above 0 (logits that are not finite)
+  }
+  const float lse = zmax + __logf(r.s);
+  a->actions[c.r] = any ? r.ba : -1;
+  if (c.bad) atomicOr(a->err, c.bad);
+  if (a->logp) a->logp[c.r] = any ? r.bz - lse : 0.f;
+  if (a->entropy) a->entropy[c.r] = any ? lse - r.sz / r.s : 0.f;
+  if (a->value) a->value[c.r] = c.bad ? 0.f : val;
 }
 
-// Masked argmax over the lane pair (n, n + 32), logits store, action store
-// (or the RL-rollout outputs). RL: 0 = greedy route only, 1 = RL outputs
-// only, 2 = either, chosen by a.rl at run time.
+// Stores the four consecutive logits act .. act + 3 of a row, those below A.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_logits(KernArgs a, float* row, int act, float z0, float z1, float z2,
+                                             float z3) {
+  if (act + 4 <= a->A) {
+    *(f32x4u*)(row + act) = (f32x4u){z0, z1, z2, z3};
+  } else {
+    if (act < a->A) row[act] = z0;
+    if (act + 1 < a->A) row[act + 1] = z1;
+    if (act + 2 < a->A) row[act + 2] = z2;
+  }
+}
+
+// Masked argmax over the lane pair (n, n + 32), logits store, action store (or
+// the RL-rollout outputs). Lane (n, g) holds the actions 32 T + 8 (v / 4) + 4 g
+// + v % 4 of its row. RL: 0 = greedy route only, 1 = RL outputs only, 2 =
+// either, chosen by a->rl at run time.
 template <int AT, int RL = 2>
-__device__ __forceinline__ void epilogue(const RouteArgs& a, const RowCtx& c, f32x16 (&acc)[AT],
-                                         const float* bias, int g) {
-  float best = 0.f;
-  int ba = -1;
+__device__ __forceinline__ void epilogue(const RowCtx& c, const f32x16 (&acc)[AT], int g) {
+  const KernArgs a = late_args();
+  const bool rl = RL == 1 || (RL == 2 && a->rl);
+  // bit 32 T + 8 j + i: action 32 T + 8 j + 4 g + i is masked
+  uint64_t am = c.amask;
+  asm volatile("" : "+v"(am));   // the shifted mask is formed here, not kept beside the mask since the row's setup
+  const uint64_t inv = (uint64_t)((int64_t)~am >> (4 * g));
+  const uint32_t mw[2] = {(uint32_t)inv, (uint32_t)(inv >> 32)};
+  constexpr int AA = AT < 2 ? AT : 2;   // tiles with actions (at most 64; a third tile holds the value row only)
+  float zm[AA][16];
+  float best = __uint_as_float(0xffffffffu);
 #pragma unroll
-  for (int T = 0; T < AT; ++T) {
+  for (int T = 0; T < AA; ++T) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int act = 32 * T + 8 * (v >> 2) + 4 * g + (v & 3);
-      const float z = bias ? acc[T][v] + bias[(T * 2 + g) * 16 + v] : acc[T][v];
-      acc[T][v] = z;
-      if (act < a.A && ((c.amask >> act) & 1ull)) {
-        if (ba < 0 || z > best) { best = z; ba = act; }
-      }
-    }
+    for (int v = 0; v < 16; ++v) zm[T][v] = mask_logit(acc[T][v], bit_ones(mw[T], 8 * (v >> 2) + (v & 3)));
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) best = max3(best, zm[T][v], zm[T][v + 1]);
   }
-  const float ob = __shfl_xor(best, 32, 64);
-  const int oa = __shfl_xor(ba, 32, 64);
-  if (oa >= 0 && (ba < 0 || ob > best || (ob == best && oa < ba))) { best = ob; ba = oa; }
-  if (RL == 1 || (RL == 2 && a.rl)) {
-    rl_outputs<AT>(a, c, acc, g, best, ba);
-  } else if (c.live && g == 0) {
-    a.actions[c.r] = c.bad ? -1 : ba;
-    if (c.bad) atomicOr(a.err, c.bad);
+  {
+    int32_t x, y;
+    swap_halves<32>(as_int(best), x, y);
+    best = max3(__int_as_float(x), __int_as_float(y), __int_as_float(y));
   }
-  if (!c.live) return;
-  if (a.logits) {
-    float* out = a.logits + (size_t)c.r * a.A;
+  int32_t ba = 127;
+  if (!rl || a->greedy) {   // uniform
+#pragma unroll
+    for (int T = AA - 1; T >= 0; --T)
+#pragma unroll
+      for (int v = 15; v >= 0; --v) ba = zm[T][v] == best ? 32 * T + 8 * (v >> 2) + (v & 3) : ba;
+    ba += 4 * g;
+    int32_t x, y;
+    swap_halves<32>(ba, x, y);
+    ba = x < y ? x : y;
+    // -1 when no action is valid; the first valid one when every valid logit is NaN
+    if (ba >= 64) ba = __ffsll((unsigned long long)c.amask) - 1;
+  }
+  if (rl) {
+    const bool sample = a->greedy == 0;
+    uint32_t id = 0;
+    if (sample) id = c.id >= 0 ? (uint32_t)c.id : request_id(a, c);
+    // the key schedule is formed per row group: hoisted out of the kernel's loop
+    // its 18 words would spill scalar registers into vector ones
+    uint32_t k0 = a->seed_lo, k1 = a->seed_hi;
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    RlSums r;
+    float val = 0.f;
 #pragma unroll
     for (int T = 0; T < AT; ++T) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int act = 32 * T + 8 * (v >> 2) + 4 * g + (v & 3);
-        if (act < a.A) out[act] = c.bad ? 0.f : acc[T][v];
+      for (int j = 0; j < 4; ++j) {
+        const int a0 = 32 * T + 8 * j;   // the lane pair's 8 actions: two Philox blocks
+        const float z[4] = {acc[T][4 * j], acc[T][4 * j + 1], acc[T][4 * j + 2], acc[T][4 * j + 3]};
+        if (T < AA && a0 < a->A) {        // uniform
+          const uint32_t mb = mw[T < AA ? T : 0] >> (8 * j);
+          if (sample) {
+            const uint4 w = philox10(make_uint4(id, (uint32_t)c.e, (uint32_t)((a0 >> 2) + g), 0u), k0, k1);
+            rl_block<true>(r, z, mb, best, a0 + 4 * g, w);
+          } else {
+            rl_block<false>(r, z, mb, best, a0 + 4 * g, make_uint4(0, 0, 0, 0));
+          }
+        }
+        if (a->value && (a->A >> 3) == 4 * T + j) {   // uniform: the group of row A
+          const int i = a->A & 3;
+          const float v = i == 0 ? z[0] : (i == 1 ? z[1] : (i == 2 ? z[2] : z[3]));
+          val = ((a->A >> 2) & 1) == g ? v : 0.f;
+        }
+      }
+    }
+    auto other = [](float v) { return __int_as_float(xshfl<32>(as_int(v))); };
+    rl_join(r, other(r.s), other(r.sz), other(r.bs), other(r.bz), xshfl<32>(r.ba));
+    val += other(val);   // one lane of the pair holds row A
+    if (c.live && g == 0) rl_store(a, c, r, best, ba, val);
+  } else if (c.live && g == 0) {
+    a->actions[c.r] = c.bad ? -1 : ba;
+    if (c.bad) atomicOr(a->err, c.bad);
+  }
+  if (!c.live) return;
+  if (a->logits) {
+    float* out = a->logits + (size_t)c.r * a->A;
+#pragma unroll
+    for (int T = 0; T < AT; ++T) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float z0 = c.bad ? 0.f : acc[T][4 * j], z1 = c.bad ? 0.f : acc[T][4 * j + 1];
+        const float z2 = c.bad ? 0.f : acc[T][4 * j + 2], z3 = c.bad ? 0.f : acc[T][4 * j + 3];
+        store_logits(a, out, 32 * T + 8 * j + 4 * g, z0, z1, z2, z3);
       }
     }
   }

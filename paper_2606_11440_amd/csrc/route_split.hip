@@ -68,7 +68,7 @@ struct WeightRing {
 };
 
 template <int H, int NL, int AT, int NR, int TPW>
-__global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? 4 : (NR == 2 ? 3 : 2)) void route_bf16_split(RouteArgs a_in) {
+__global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 3 : 4) : (NR == 2 ? 3 : 2)) void route_bf16_split(RouteArgs a_in) {
   // chain pools: the tick's row count is on the device
   RouteArgs a = a_in;
   if (a_in.n_total_dev) a.n_total = min(*a_in.n_total_dev, a_in.n_total);   // the caller's buffers bound it
@@ -144,10 +144,9 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? 4 : (NR == 2 ? 3 : 2))
       int32_t env[1];
       find_envs<1>(a, first, last, rows, env);
       e = env[0];
-      const ValidRaw vr = load_valid(a, e);
+      m = action_mask(a, e);
       if (a.rl && !a.greedy) id = a.ms[(size_t)e * a.M].next_id + (rows[0] - a.offsets[e]);
       bad = (qi < 0 || (int64_t)qi >= a.Q) ? IM_ERR_QIDX : 0;
-      m = mask_of(a, vr);
     }
     if (i < ROWS) {
       s_e[i] = e;
@@ -247,7 +246,7 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? 4 : (NR == 2 ? 3 : 2))
     f32x16 o[AT];
 #pragma unroll
     for (int T = 0; T < AT; ++T) o[T] = out[T][0];
-    epilogue<AT>(a, r, o, nullptr, g);
+    epilogue<AT>(r, o, g);
   }
 }
 

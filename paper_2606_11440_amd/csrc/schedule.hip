@@ -284,8 +284,7 @@ __device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext,
 }
 
 // Snapshot row entry of model m of env e from its state (one fp32 product
-// per load statistic; validity byte). `part` selects which value to write
-// (0..3: the four statistics, 4: validity), so lanes can share the work.
+// per load statistic). `part` selects the statistic (0..3).
 // The queue-depth statistic: recent dispatches / RPM limit for a blackbox
 // model (Sec. 5.5), queue length / QCAP otherwise.
 __device__ __forceinline__ float queue_stat(const SchedArgs& a, int32_t qlen, int32_t rpm,
@@ -295,8 +294,7 @@ __device__ __forceinline__ float queue_stat(const SchedArgs& a, int32_t qlen, in
 
 __device__ __forceinline__ void write_snap_part(const SchedArgs& a, int e, int m, int part,
                                                 int32_t qlen, int32_t busy, int32_t ewma,
-                                                int32_t backlog, int32_t cap, int32_t enabled,
-                                                int32_t rpm, int32_t rcnt, float inv_rpm) {
+                                                int32_t backlog, int32_t cap, int32_t rpm, int32_t rcnt, float inv_rpm) {
   float* row = a.snap + (size_t)e * snap_stride(a.M);
   const int c = cap < 0 ? 0 : (cap > IM_MAX_SLOTS ? IM_MAX_SLOTS : cap);
   switch (part) {
@@ -304,11 +302,6 @@ __device__ __forceinline__ void write_snap_part(const SchedArgs& a, int e, int m
     case 1: row[a.M + m] = (float)busy * a.inv_tab[c]; break;
     case 2: row[2 * a.M + m] = (float)ewma * a.inv_lat; break;
     case 3: row[3 * a.M + m] = (float)backlog * a.inv_tab[IM_MAX_SLOTS + 1 + c]; break;
-    case 4: {
-      uint8_t* v = (uint8_t*)(row + snap_valid_offset(a.M));
-      v[m] = (enabled != 0 && cap > 0 && qlen < a.qcap) ? 1 : 0;
-      break;
-    }
     default: break;
   }
 }
@@ -319,9 +312,18 @@ __global__ void snapshot_kernel(SchedArgs a, int e0, int ne) {
   const int64_t em = (int64_t)e0 * a.M + i;
   const int e = (int)(em / a.M), m = (int)(em - (int64_t)e * a.M);
   const ModelRec r = a.ms[em];
-  for (int part = 0; part < 5; ++part)
-    write_snap_part(a, e, m, part, r.qlen, r.busy, r.ewma, r.backlog, r.cap, r.enabled,
-                    r.rpm_limit, r.rpm_count, r.inv_rpm);
+  for (int part = 0; part < 4; ++part)
+    write_snap_part(a, e, m, part, r.qlen, r.busy, r.ewma, r.backlog, r.cap, r.rpm_limit, r.rpm_count,
+                    r.inv_rpm);
+  if (m == 0) {   // the env's valid actions
+    const uint64_t kmask = a.K >= 64 ? ~0ull : (1ull << a.K) - 1ull;
+    uint64_t am = 0;
+    for (int j = 0; j < a.M; ++j) {
+      const ModelRec& q = a.ms[em + j];
+      if (q.enabled != 0 && q.cap > 0 && q.qlen < a.qcap) am |= kmask << (j * a.K);
+    }
+    *reinterpret_cast<uint64_t*>(a.snap + (size_t)e * snap_stride(a.M) + snap_mask_offset(a.M)) = am;
+  }
 }
 
 __device__ __forceinline__ int32_t wave_sum32(int32_t v) {
@@ -1126,7 +1128,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     }
   }
   // Snapshot row for the next tick's route step: lane i < 4M writes
-  // statistic i / M of model i % M, lanes m < M the validity bytes.
+  // statistic i / M of model i % M, lane 0 the mask of the valid actions.
   if (ballot(ml && (L.chg & CH_STATS)) != 0) {
     float* row = a.snap + (size_t)e * snap_stride(M);
     const float inv_rpm_l = __int_as_float(inv_rpm_bits);
@@ -1146,10 +1148,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
       const float v = sidx == 0 ? v0 : (sidx == 1 ? (float)vb * ib : (sidx == 2 ? (float)vw * a.inv_lat : (float)vk * ik));
       if (i < 4 * M) row[i] = v;
     }
-    if (ml) {
-      uint8_t* vb8 = (uint8_t*)(row + snap_valid_offset(M));
-      vb8[lane] = (en_l != 0 && cap_l > 0 && L.qlen < a.qcap) ? 1 : 0;
-    }
+    // the valid actions: lane i for action i of model i / K
+    const uint64_t vm = ballot(ml && en_l != 0 && cap_l > 0 && L.qlen < a.qcap);
+    const int am_l = K == 1 ? lane : (int)__umulhi((uint32_t)lane, kmag);
+    const uint64_t am = ballot(lane < a.A && ((vm >> am_l) & 1ull));
+    if (lane == 0) *reinterpret_cast<uint64_t*>(row + snap_mask_offset(M)) = am;
   }
   int64_t* envc_p = a.env_cnt + (size_t)e * kEnvCnt;
   if (nrows > 0) {
