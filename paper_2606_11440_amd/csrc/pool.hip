@@ -136,13 +136,11 @@ uint16_t to_bf16(float f) {
 int bf16_k(int layer, int kb, int g, int j) {
   return layer == 0 ? 16 * kb + 8 * g + j : 16 * kb + 8 * (j >> 2) + 4 * g + (j & 3);
 }
-// Feature read by K step i of lane group q (lane / 16) in the fp32 kernel's
-// 16x16x4 MFMA order: layer 1 in natural order; later layers in the previous
-// layer's accumulator order (tile i / 4, register i % 4: feature 16 (i / 4)
-// + 4 q + i % 4).
-int f32_k(int layer, int i, int q) {
-  return layer == 0 ? 4 * i + q : 16 * (i >> 2) + 4 * q + (i & 3);
-}
+// Feature read by K step i of lane group q (lane / 16) in the fp32 kernels'
+// 16x16x4 MFMA order: 16 (i / 4) + 4 q + i % 4. For the deeper layers that is
+// the previous layer's accumulator order (tile i / 4, register i % 4); for
+// layer 1 it lets a lane fetch the four steps of a group in one 16-byte load.
+int f32_k(int i, int q) { return 16 * (i >> 2) + 4 * q + (i & 3); }
 
 template <class T>
 im_status upload(im_pool* p, T** dst, const std::vector<T>& src) {
@@ -366,14 +364,14 @@ im_status im_pool_create(const im_pool_desc* desc, const float* const* W, const 
     } else {
       // 16-row output tiles, K steps of 4 grouped by four: [To][group][lane][4]
       const int TO16 = (outw + 15) / 16;
-      const int KS = (in + 3) / 4, KG = (KS + 3) / 4;
+      const int KG = (in + 15) / 16, KS = 4 * KG;
       if (l == 0) p->k1 = KS;
       std::vector<float> pk((size_t)TO16 * KG * 64 * 4, 0.f);
       for (int To = 0; To < TO16; ++To)
         for (int i = 0; i < KS; ++i)
           for (int lane = 0; lane < 64; ++lane) {
             const int o = 16 * To + (lane & 15);
-            const int k = f32_k(l, i, lane >> 4);
+            const int k = f32_k(i, lane >> 4);
             if (o < outw && k < in)
               pk[(((size_t)To * KG + (i >> 2)) * 64 + lane) * 4 + (i & 3)] = Wl[(size_t)o * in + k];
           }

@@ -183,6 +183,29 @@ __device__ __forceinline__ void layer16(const f32x4* W, const float* bias, const
   }
 }
 
+// Features 16 g + 4 q .. + 3 of a row, the four K steps of group g in lane group
+// q (fp32 pools): one 16-byte load of the embedding or of the env's load
+// statistics where the embedding width is a multiple of 4.
+__device__ __forceinline__ f32x4 feats16(const RouteArgs& a, const RowCtx& c, int g, int q) {
+  const int k = 16 * g + 4 * q;
+  const float* emb = (const float*)a.emb + (size_t)c.q * a.embed_dim;
+  if ((a.embed_dim & 3) == 0) {
+    const int k2 = k - a.embed_dim;   // 4 M is a multiple of 4 too: the four are of one kind
+    if (k2 < 0) {
+      const f32x4u v = *(const f32x4u*)(emb + k);   // the table itself may be only 4-byte aligned
+      return (f32x4){v.x, v.y, v.z, v.w};
+    }
+    if (k2 < 4 * a.M) return *(const f32x4*)(a.snap + (size_t)c.e * snap_stride(a.M) + k2);
+    f32x4 x = {};
+    if (k2 == 4 * a.M) x.x = (float)c.budget * a.inv_bud;
+    return x;
+  }
+  f32x4 x;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) x[j] = k + j < a.embed_dim ? emb[k + j] : tail_feature(a, c, k + j);
+  return x;
+}
+
 template <int H, int NL, int AT>
 __global__ __launch_bounds__(256) void route_f32(RouteArgs a_in) {
   // chain pools: the tick's row count is on the device
@@ -201,21 +224,12 @@ __global__ __launch_bounds__(256) void route_f32(RouteArgs a_in) {
   constexpr int TH = H / 16;   // hidden output tiles
   constexpr int KGH = H / 16;  // K step groups over a hidden layer (4 steps of 4 features)
   const f32x4* W1 = (const f32x4*)a.W[0];
-  const float* emb = (const float*)a.emb + (size_t)c.q * a.embed_dim;
-  // layer 1: K step s, lane group q carries feature 4 s + q; four steps per group
+  // layer 1: the K steps of group g carry features 16 g + 4 q .. + 3 in lane group q
   const int KG1 = (a.k1 + 3) / 4;
   f32x4 h1[TH];
 #pragma unroll
   for (int T = 0; T < TH; ++T) h1[T] = *(const f32x4*)(a.bias[0] + (T * 4 + q) * 4);
-  auto feats = [&](int g) {
-    f32x4 x;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = 16 * g + 4 * j + q;
-      x[j] = k < a.embed_dim ? emb[k] : tail_feature(a, c, k);
-    }
-    return x;
-  };
+  auto feats = [&](int g) { return feats16(a, c, g, q); };
   f32x4 x = feats(0);
   f32x4 wn[TH];
 #pragma unroll
@@ -260,140 +274,179 @@ __global__ __launch_bounds__(256) void route_f32(RouteArgs a_in) {
   epilogue16<AT>(c, out, q);
 }
 
-// TQ output tiles [To0, To0 + TQ) of a layer over its hidden input, read from
-// LDS (`hs`: tile g's 16-byte words at hs[g 64 + lane]) while the weights
-// (W[(To KG + g) 64 + lane], 4 floats) come through the caches D groups
-// ahead. Consecutive MFMAs use different accumulators: the tiles' own chains
-// when there are four or more, else four partial sums per tile.
-template <int TQ, int KG, int D>
-__device__ __forceinline__ void layer16_lds(const f32x4* W, const float* bias, const f32x4* hs, int To0,
-                                            int lane, int q, f32x4 (&out)[TQ]) {
-  constexpr int NP = TQ >= 4 ? 1 : 4;
-  constexpr int DD = D < KG ? D : KG;
-  f32x4 wr[DD][TQ];
+// TQ output tiles [To0, To0 + TQ) of a layer for NR row tiles over KG groups of
+// inputs in LDS (`hs`: group g's 16-byte words of row tile j at
+// hs[(g NR + j) 64 + lane]) while the weights (W[(To stride + g) 64 + lane],
+// 4 floats) come through the caches D groups ahead. acc[t][j][0] holds the
+// bias; NP partial sums per tile where too few tiles would otherwise share an
+// accumulator between consecutive MFMAs.
+template <int TQ, int NR, int NP, int D>
+__device__ __forceinline__ void layer16_lds(const f32x4* W, int stride, int KG, const f32x4* hs, int To0, int lane,
+                                            f32x4 (&acc)[TQ][NR][NP]) {
+  const f32x4* Wl = W + (size_t)To0 * stride * 64 + lane;
+  f32x4 wr[D][TQ];
 #pragma unroll
-  for (int g = 0; g < DD; ++g)
+  for (int d = 0; d < D; ++d)
 #pragma unroll
-    for (int t = 0; t < TQ; ++t) wr[g][t] = W[((To0 + t) * KG + g) * 64 + lane];
-  f32x4 acc[TQ][NP];
+    for (int t = 0; t < TQ; ++t) wr[d][t] = Wl[(t * stride + (d < KG ? d : KG - 1)) * 64];
+  for (int g0 = 0; g0 < KG; g0 += D) {
 #pragma unroll
-  for (int t = 0; t < TQ; ++t) {
-    acc[t][0] = *(const f32x4*)(bias + ((To0 + t) * 4 + q) * 4);
+    for (int d = 0; d < D; ++d) {
+      const int g = g0 + d;
+      if (g < KG) {
+        f32x4 b[NR], w[TQ];
 #pragma unroll
-    for (int i = 1; i < NP; ++i) acc[t][i] = f32x4{};
-  }
-  f32x4 bn = hs[lane];
+        for (int j = 0; j < NR; ++j) b[j] = hs[(g * NR + j) * 64 + lane];
+        const int gn = g + D < KG ? g + D : KG - 1;
 #pragma unroll
-  for (int g = 0; g < KG; ++g) {
-    const f32x4 b = bn;
-    if (g + 1 < KG) bn = hs[(g + 1) * 64 + lane];
-    f32x4 w[TQ];
+        for (int t = 0; t < TQ; ++t) {
+          w[t] = wr[d][t];
+          wr[d][t] = Wl[(t * stride + gn) * 64];
+        }
 #pragma unroll
-    for (int t = 0; t < TQ; ++t) w[t] = wr[g % DD][t];
-    if (g + DD < KG) {
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int t = 0; t < TQ; ++t) wr[g % DD][t] = W[((To0 + t) * KG + g + DD) * 64 + lane];
+          for (int t = 0; t < TQ; ++t)
+#pragma unroll
+            for (int j = 0; j < NR; ++j) acc[t][j][i % NP] = mfma16_f32(w[t][i], b[j][i], acc[t][j][i % NP]);
+      }
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int t = 0; t < TQ; ++t) acc[t][j % NP] = mfma16_f32(w[t][j], b[j], acc[t][j % NP]);
   }
+}
+
+// The output layer of one row tile: its input groups are NR apart in LDS.
+template <int AT, int NR, int NP, int D>
+__device__ __forceinline__ void layer16_out(const f32x4* W, int KG, const f32x4* hs, int lane, f32x4 (&acc)[AT][1][NP]) {
+  f32x4 wr[D][AT];
 #pragma unroll
-  for (int t = 0; t < TQ; ++t) {
-    f32x4 r = acc[t][0];
+  for (int d = 0; d < D; ++d)
 #pragma unroll
-    for (int i = 1; i < NP; ++i) r += acc[t][i];
-    out[t] = r;
+    for (int t = 0; t < AT; ++t) wr[d][t] = W[(t * KG + (d < KG ? d : KG - 1)) * 64 + lane];
+  for (int g0 = 0; g0 < KG; g0 += D) {   // KG is a multiple of 4
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int g = g0 + d;
+      const f32x4 b = hs[g * NR * 64 + lane];
+      const int gn = g + D < KG ? g + D : KG - 1;
+#pragma unroll
+      for (int t = 0; t < AT; ++t) {
+        const f32x4 w = wr[d][t];
+        wr[d][t] = W[(t * KG + gn) * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[t][0][i % NP] = mfma16_f32(w[i], b[i], acc[t][0][i % NP]);
+      }
+    }
   }
 }
 
 // fp32 policies with hidden widths in whole tile quads, feature-split: one
-// block of 4 waves per 16-row tile, wave w computing output tiles
-// [w TH/4, (w + 1) TH/4) of each hidden layer; the block exchanges a layer's
-// activations through LDS (one 16-row x H buffer, h1 and then h2), and wave 0
-// computes the output layer and the epilogue. Each wave does about a quarter
-// of a tile's MFMAs, so four waves share each SIMD and hide each other's
-// latencies, and a tick slightly above a multiple of the machine's SIMDs
-// adds quarter tiles rather than whole ones.
-template <int H, int NL, int AT>
+// block of 4 waves per 16 NR rows, wave w computing output tiles
+// [w TH/4, (w + 1) TH/4) of each hidden layer; the block exchanges features and
+// activations through LDS (one buffer, rewritten layer by layer), and wave j
+// computes the output layer and the epilogue of row tile j. The features come
+// in once per block, a group (four K steps) per wave in turn.
+template <int H, int NL, int AT, int NR>
 __global__ __launch_bounds__(256) void route_f32s(RouteArgs a_in) {
   // chain pools: the tick's row count is on the device
   RouteArgs a = a_in;
   if (a_in.n_total_dev) a.n_total = min(*a_in.n_total_dev, a_in.n_total);   // the caller's buffers bound it
-  constexpr int TH = H / 16, TQ = TH / 4, KGH = H / 16;
+  constexpr int TH = H / 16, TQ = TH / 4, KGH = H / 16, ROWS = 16 * NR;
+  constexpr int KC = KGH < 8 ? 8 : KGH;      // groups of features in LDS at a time
+  constexpr int NP = TQ >= 4 ? 1 : 4;        // partial sums of the hidden layers after the first
+  constexpr int NPO = AT >= 4 ? 1 : 4;       // of the output layer
   static_assert(TH % 4 == 0, "hidden tiles split four ways");
-  __shared__ f32x4 hs[TH * 64];
+  __shared__ f32x4 hs[KC * NR * 64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, q = lane >> 4;
-  const int32_t row0 = (int32_t)blockIdx.x * 16;
+  const int32_t row0 = (int32_t)blockIdx.x * ROWS;
   if (row0 >= a.n_total) return;   // the whole block (chain pools' bound launch)
-  const int32_t rl = row0 + 15 < a.n_total ? row0 + 15 : a.n_total - 1;
-  const int32_t rows[1] = {row0 + n};
-  const int32_t rsel[1] = {rows[0] < a.n_total ? rows[0] : a.n_total - 1};
-  int32_t envs[1];
-  find_envs<1>(a, row0, rl, rsel, envs);
-  const RowCtx c = row_setup_env(a, rows[0], envs[0]);
   const int T0 = wave * TQ;
-  // layer 1 (this wave's tiles): K step s, lane group q carries feature 4 s + q
-  const f32x4* W1 = (const f32x4*)a.W[0];
-  const float* emb = (const float*)a.emb + (size_t)c.q * a.embed_dim;
   const int KG1 = (a.k1 + 3) / 4;
-  f32x4 h1[TQ];
+  f32x4 bias1[TQ];
 #pragma unroll
-  for (int t = 0; t < TQ; ++t) h1[t] = *(const f32x4*)(a.bias[0] + ((T0 + t) * 4 + q) * 4);
-  auto feats = [&](int g) {
-    f32x4 x;
+  for (int t = 0; t < TQ; ++t) bias1[t] = *(const f32x4*)(a.bias[0] + ((T0 + t) * 4 + q) * 4);
+  const int32_t rlast = min(row0 + ROWS - 1, a.n_total - 1);
+  int32_t rows[NR], rsel[NR], envs[NR];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = 16 * g + 4 * j + q;
-      x[j] = k < a.embed_dim ? emb[k] : tail_feature(a, c, k);
-    }
-    return x;
-  };
-  f32x4 x = feats(0);
-  f32x4 wn[TQ];
-#pragma unroll
-  for (int t = 0; t < TQ; ++t) wn[t] = W1[((T0 + t) * KG1) * 64 + lane];
-  for (int g = 0; g < KG1; ++g) {
-    f32x4 wc[TQ];
-#pragma unroll
-    for (int t = 0; t < TQ; ++t) wc[t] = wn[t];
-    const f32x4 xc = x;
-    if (g + 1 < KG1) {
-      x = feats(g + 1);
-#pragma unroll
-      for (int t = 0; t < TQ; ++t) wn[t] = W1[((T0 + t) * KG1 + g + 1) * 64 + lane];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int t = 0; t < TQ; ++t) h1[t] = mfma16_f32(wc[t][j], xc[j], h1[t]);
+  for (int j = 0; j < NR; ++j) {
+    rows[j] = row0 + 16 * j + n;
+    rsel[j] = min(rows[j], rlast);
   }
+  find_envs<NR>(a, row0, rlast, rsel, envs);
+  RowCtx c[NR];
 #pragma unroll
-  for (int t = 0; t < TQ; ++t) {
+  for (int j = 0; j < NR; ++j) c[j] = row_setup_env(a, rows[j], envs[j]);
+
+  f32x4 h[TQ][NR][1];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) h1[t][r] = relu(h1[t][r]);
-    hs[(T0 + t) * 64 + lane] = h1[t];
-  }
-  __syncthreads();
-  if constexpr (NL == 3) {
-    f32x4 h2[TQ];
-    layer16_lds<TQ, KGH, 2>((const f32x4*)a.W[1], a.bias[1], hs, T0, lane, q, h2);
-    __syncthreads();   // every wave is done reading h1
+  for (int t = 0; t < TQ; ++t)
 #pragma unroll
-    for (int t = 0; t < TQ; ++t) {
+    for (int j = 0; j < NR; ++j) h[t][j][0] = bias1[t];
+  for (int g0 = 0; g0 < KG1; g0 += KC) {
+    const int kn = KG1 - g0 < KC ? KG1 - g0 : KC;
+    if (g0 != 0) __syncthreads();   // every wave is done with the previous features
+    for (int g = wave; g < kn; g += 4)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) h2[t][r] = relu(h2[t][r]);
-      hs[(T0 + t) * 64 + lane] = h2[t];
-    }
+      for (int j = 0; j < NR; ++j) hs[(g * NR + j) * 64 + lane] = feats16(a, c[j], g0 + g, q);
     __syncthreads();
+    layer16_lds<TQ, NR, 1, 2>((const f32x4*)a.W[0] + g0 * 64, KG1, kn, hs, T0, lane, h);
   }
-  if (wave != 0) return;
-  f32x4 out[AT];
-  layer16_lds<AT, KGH, 2>((const f32x4*)a.W[NL - 1], a.bias[NL - 1], hs, 0, lane, q, out);
-  epilogue16<AT>(c, out, q);
+  auto put = [&](f32x4 (&v)[TQ][NR][1]) {   // ReLU and exchange
+    __syncthreads();   // every wave is done reading the layer's input
+#pragma unroll
+    for (int t = 0; t < TQ; ++t)
+#pragma unroll
+      for (int j = 0; j < NR; ++j) {
+        f32x4 x = v[t][j][0];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = relu(x[r]);
+        hs[((T0 + t) * NR + j) * 64 + lane] = x;
+      }
+    __syncthreads();
+  };
+  put(h);
+  if constexpr (NL == 3) {
+    f32x4 acc[TQ][NR][NP];
+#pragma unroll
+    for (int t = 0; t < TQ; ++t)
+#pragma unroll
+      for (int j = 0; j < NR; ++j) {
+        acc[t][j][0] = *(const f32x4*)(a.bias[1] + ((T0 + t) * 4 + q) * 4);
+#pragma unroll
+        for (int i = 1; i < NP; ++i) acc[t][j][i] = f32x4{};
+      }
+    layer16_lds<TQ, NR, NP, 2>((const f32x4*)a.W[1], KGH, KGH, hs, T0, lane, acc);
+#pragma unroll
+    for (int t = 0; t < TQ; ++t)
+#pragma unroll
+      for (int j = 0; j < NR; ++j) {
+        f32x4 r = acc[t][j][0];
+#pragma unroll
+        for (int i = 1; i < NP; ++i) r += acc[t][j][i];
+        h[t][j][0] = r;
+      }
+    put(h);
+  }
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    if (wave != j) continue;   // uniform
+    f32x4 acc[AT][1][NPO];
+#pragma unroll
+    for (int T = 0; T < AT; ++T) {
+      acc[T][0][0] = *(const f32x4*)(a.bias[NL - 1] + (T * 4 + q) * 4);
+#pragma unroll
+      for (int i = 1; i < NPO; ++i) acc[T][0][i] = f32x4{};
+    }
+    layer16_out<AT, NR, NPO, 4>((const f32x4*)a.W[NL - 1], KGH, hs + j * 64, lane, acc);
+    f32x4 out[AT];
+#pragma unroll
+    for (int T = 0; T < AT; ++T) {
+      out[T] = acc[T][0][0];
+      if constexpr (NPO == 4) out[T] = (out[T] + acc[T][0][1]) + (acc[T][0][2] + acc[T][0][3]);
+    }
+    epilogue16<AT>(c[j], out, q);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1108,24 +1161,29 @@ __global__ void role_projection_kernel(const uint16_t* w_role, const uint16_t* r
 
 typedef void (*RouteKernel)(RouteArgs);
 
+template <int H, int NL, int NR>
+RouteKernel pick_f32s(int at) {
+  return at == 1 ? route_f32s<H, NL, 1, NR>
+                 : (at == 2 ? route_f32s<H, NL, 2, NR> : (at == 3 ? route_f32s<H, NL, 3, NR> : route_f32s<H, NL, 4, NR>));
+}
 template <int H, int NL>
-RouteKernel pick_f32(int at) {
+RouteKernel pick_f32(int at, int nr) {
   // at: output tiles of 16 (fp32 pools); feature-split kernel when the hidden
-  // tiles split four ways
+  // tiles split four ways, nr row tiles per block
   if constexpr ((H / 16) % 4 == 0)
-    return at == 1 ? route_f32s<H, NL, 1>
-                   : (at == 2 ? route_f32s<H, NL, 2> : (at == 3 ? route_f32s<H, NL, 3> : route_f32s<H, NL, 4>));
-  return at == 1 ? route_f32<H, NL, 1>
-                 : (at == 2 ? route_f32<H, NL, 2> : (at == 3 ? route_f32<H, NL, 3> : route_f32<H, NL, 4>));
+    return nr == 1 ? pick_f32s<H, NL, 1>(at) : pick_f32s<H, NL, 2>(at);
+  else
+    return at == 1 ? route_f32<H, NL, 1>
+                   : (at == 2 ? route_f32<H, NL, 2> : (at == 3 ? route_f32<H, NL, 3> : route_f32<H, NL, 4>));
 }
 
 template <int NL>
-RouteKernel pick(int hidden, int at) {
+RouteKernel pick(int hidden, int at, int nr) {
   switch (hidden) {
-    case 32: return pick_f32<32, NL>(at);
-    case 64: return pick_f32<64, NL>(at);
-    case 128: return pick_f32<128, NL>(at);
-    case 256: return pick_f32<256, NL>(at);
+    case 32: return pick_f32<32, NL>(at, nr);
+    case 64: return pick_f32<64, NL>(at, nr);
+    case 128: return pick_f32<128, NL>(at, nr);
+    case 256: return pick_f32<256, NL>(at, nr);
   }
   return nullptr;
 }
@@ -1227,7 +1285,7 @@ bool route_supported(int dtype, int hidden, int n_layers, int out_tiles) {
   if (n_layers != 2 && n_layers != 3) return false;
   if (out_tiles < 1 || out_tiles > (dtype == IM_F32 ? 4 : 3)) return false;
   if (dtype == IM_BF16) return split_supported(hidden);
-  return (n_layers == 2 ? pick<2>(hidden, out_tiles) : pick<3>(hidden, out_tiles)) != nullptr;
+  return (n_layers == 2 ? pick<2>(hidden, out_tiles, 1) : pick<3>(hidden, out_tiles, 1)) != nullptr;
 }
 
 hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers, int out_tiles,
@@ -1275,9 +1333,15 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
     }
   }
   if (dtype == IM_BF16) return launch_split(a, hidden, n_layers, out_tiles, s);
-  RouteKernel k = n_layers == 2 ? pick<2>(hidden, out_tiles) : pick<3>(hidden, out_tiles);
-  // blocks of 4 waves: 16 rows per wave (hidden width 32) or 16 rows per block (feature-split)
-  const int rows = hidden % 64 == 0 ? 16 : 64;
+  // One 16-row tile per block while the blocks fit one per compute unit (a
+  // block's latency bounds the launch), else two, which halves the weight bytes
+  // from L2 per MFMA. us per launch at 1 / 2 tiles: 86 -> 256 -> 256 -> 15 at
+  // 4,096 rows 12.5 / 17.8, 8,192 rows 21.2 / 18.4, 16,384 rows 37.8 / 32.7;
+  // 449 -> 256 -> 64 at 4,096 rows 22.6 / 30.8, 16,384 rows 58.0 / 49.4.
+  const int nr = a.n_total <= 16 * a.cus ? 1 : 2;
+  RouteKernel k = n_layers == 2 ? pick<2>(hidden, out_tiles, nr) : pick<3>(hidden, out_tiles, nr);
+  // blocks of 4 waves: 16 rows per wave (hidden width 32) or 16 nr rows per block (feature-split)
+  const int rows = hidden % 64 == 0 ? 16 * nr : 64;
   const unsigned blocks = (unsigned)((a.n_total + rows - 1) / rows);
   hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
 #pragma unroll
   for (int t = 0; t < TPW; ++t) acc[t][0] = *(const f32x16*)(a.bias[0] + ((T0 + t) * 2 + g) * 16);
 
-  const bool aligned = (a.embed_dim & 7) == 0;
+  const bool aligned = (a.embed_dim & 7) == 0 && ((uintptr_t)a.emb & 15) == 0;   // 16-byte aligned rows
   const int ke = aligned ? a.embed_dim / 16 : 0;   // K blocks that are all embedding
   int32_t q[NR];
 #pragma unroll
