@@ -27,6 +27,7 @@ static_assert(sizeof(ModelRec) == 64, "ModelRec layout");
 
 constexpr int kFront = 64;       // front capacity (one entry per lane)
 constexpr int kRpmWindow = 60;   // blackbox dispatch window (ticks; App. C: 60 s)
+constexpr int kDualShards = 1024;   // pairs of running totals of the dual update (contention of the atomics)
 constexpr int kRpmRing = 64;     // bytes per (env, model) of the per-tick dispatch ring
 
 // Per-env snapshot row read by the route step, written by the schedule step
@@ -166,6 +167,7 @@ struct SchedArgs {
   ModelRec* ms;
   int64_t* cnt;       // [E*M*C_NUM]
   int64_t* env_cnt;   // [E*kEnvCnt] arrived, rej_nomodel, completed queries, on-time queries
+  int64_t* dual_shards;  // [kDualShards][2] completions (chains: completed queries), Q16 cost; env e in e % kDualShards
   int64_t* hist;      // [E*A]
   int4* slots;        // [E*M*S]
   int4* front;        // [E*M*kFront]
@@ -180,13 +182,12 @@ struct SchedArgs {
 };
 
 // Host-side launchers (defined in the .hip files).
-// Dual update (Eq. 7): acc [2] device accumulators (zero between calls), last
-// [2] totals at the previous update, lambda device in/out.
-// env_cnt (chain pools, else NULL): queries are counted from its completed-query
-// column instead of the per-model completions.
-hipError_t launch_dual_update(const int64_t* cnt, int64_t n_em, const int64_t* env_cnt, int64_t n_env,
-                              unsigned long long* acc, int64_t* last, double eta, double lambda_max,
-                              double* lambda, hipStream_t s);
+// Dual update (Eq. 7): shards [kDualShards][2] running totals kept by the
+// schedule step, last [2] totals at the previous update, lambda device in/out.
+hipError_t launch_dual_update(const int64_t* shards, int64_t* last, double eta, double lambda_max, double* lambda,
+                              hipStream_t s);
+// The shards from the counters (after the host wrote those).
+hipError_t launch_dual_recount(const SchedArgs& a, bool chain, hipStream_t s);
 bool route_supported(int dtype, int hidden, int n_layers, int out_tiles);
 bool dual_supported(int embed_dim, int out_rows);
 // bf16 MLP policies of any shape, features split over a block's waves (route_split.hip).

@@ -42,7 +42,7 @@ struct im_pool {
   int64_t act_cap = 0;
   void* W_res = nullptr;                    // dual-pathway executor: resource-layer fragments
   float* dual_p = nullptr;                  // dual-pathway executor: fp32 parameter block
-  unsigned long long* dual_acc = nullptr;   // [3] completions, Q16 cost, block tickets (zero between calls)
+  int64_t* dual_shards = nullptr;           // [kDualShards][2] running totals of completions and Q16 cost
   int64_t* dual_last = nullptr;             // [2] totals at the previous dual update
   // multi-step chains: pending calls [2][E * pend_cap] and their counts
   // [2][E] (by tick parity), chain words of front, pool and slot entries, the
@@ -186,7 +186,7 @@ void free_pool(im_pool* p) {
     if (p->bias[l]) (void)hipFree(p->bias[l]);
   }
   void* bufs[] = {p->inv_tab, p->ms, p->cnt, p->env_cnt, p->hist, p->slots,
-                  p->front, p->qpool, p->snap, p->err, p->act_buf, p->dual_acc, p->dual_last,
+                  p->front, p->qpool, p->snap, p->err, p->act_buf, p->dual_shards, p->dual_last,
                   p->rpm_ring, p->W_res, p->dual_p, p->pend, p->pcnt, p->front_ext,
                   p->pool_ext, p->slot_ext, p->roff, p->n_rows, p->rq, p->rb, p->rr};
   for (void* b : bufs) if (b) (void)hipFree(b);
@@ -276,7 +276,7 @@ im_status init_state(im_pool* p, const int32_t* capacity, hipStream_t s) {
   if (st == IM_OK) st = zalloc(p, &p->rpm_ring, EM * (size_t)im::kRpmRing);
   if (st == IM_OK) st = zalloc(p, &p->snap, (size_t)d.n_envs * im::snap_stride(d.n_models));
   if (st == IM_OK) st = zalloc(p, &p->err, 1);
-  if (st == IM_OK) st = zalloc(p, &p->dual_acc, 3);
+  if (st == IM_OK) st = zalloc(p, &p->dual_shards, 2 * im::kDualShards);
   if (st == IM_OK) st = zalloc(p, &p->dual_last, 2);
   if (st == IM_OK && p->chains) {
     const size_t E = (size_t)d.n_envs;
@@ -705,6 +705,7 @@ static im::SchedArgs sched_args(im_pool* p) {
   a.ms = p->ms;
   a.cnt = p->cnt;
   a.env_cnt = p->env_cnt;
+  a.dual_shards = p->dual_shards;
   a.hist = p->hist;
   a.slots = p->slots;
   a.front = p->front;
@@ -759,9 +760,7 @@ im_status im_dual_update(im_pool* p, double eta, double lambda_max, double* lamb
   if (!p) return fail(nullptr, IM_EINVAL, "pool is NULL");
   if (!lambda) return fail(p, IM_EINVAL, "lambda is NULL");
   if (!(eta >= 0.0) || !(lambda_max >= 0.0)) return fail(p, IM_EINVAL, "eta and lambda_max must be >= 0");
-  IM_HIP(p, im::launch_dual_update(p->cnt, (int64_t)p->d.n_envs * p->d.n_models,
-                                   p->chains ? p->env_cnt : nullptr, p->d.n_envs, p->dual_acc,
-                                   p->dual_last, eta, lambda_max, lambda, (hipStream_t)stream));
+  IM_HIP(p, im::launch_dual_update(p->dual_shards, p->dual_last, eta, lambda_max, lambda, (hipStream_t)stream));
   return IM_OK;
 }
 
@@ -1105,6 +1104,7 @@ static im_status write_state_impl(im_pool* p, int32_t env_begin, int32_t env_cou
     IM_HIP(p, hipMemcpy(p->hist + (size_t)env_begin * A, hist, (size_t)env_count * A * 8, hipMemcpyHostToDevice));
   }
   IM_HIP(p, im::launch_snapshot(sched_args(p), env_begin, env_count, nullptr));
+  IM_HIP(p, im::launch_dual_recount(sched_args(p), p->chains, nullptr));
   IM_HIP(p, hipDeviceSynchronize());
   p->t = tick;
   return IM_OK;

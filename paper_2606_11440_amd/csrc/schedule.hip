@@ -1106,7 +1106,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
           case C_WAIT_SUM: x = mw[MW_WAIT][m]; break;
           default: x = (int64_t)md[MD_COST][m]; break;
         }
-        if (x != 0) counter_add(a.cnt + (em0 + m) * C_NUM + c, x);
+        if (x != 0) {
+          counter_add(a.cnt + (em0 + m) * C_NUM + c, x);
+          // the dual update's running totals (chain pools count queries below)
+          if (c == C_COST_Q16 || (!CHAIN && c == C_COMPLETED))
+            counter_add(a.dual_shards + 2 * (e % kDualShards) + (c == C_COST_Q16 ? 1 : 0), x);
+        }
       }
     }
   }
@@ -1165,42 +1170,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   }
   if constexpr (CHAIN) {
     if (lane == 0) a.pcnt[(size_t)((t + 1) & 1) * a.E + e] = pn;
-    if (lane == 0 && q_done != 0) counter_add(envc_p + E_Q_DONE, q_done);
+    if (lane == 0 && q_done != 0) {
+      counter_add(envc_p + E_Q_DONE, q_done);
+      counter_add(a.dual_shards + 2 * (e % kDualShards), q_done);
+    }
     if (lane == 0 && q_met != 0) counter_add(envc_p + E_Q_MET, q_met);
   }
 }
 
-// Dual update, step 1: exact int64 sums of completions and Q16 cost over every
-// (env, model) counter row (order-independent: integer atomics).
-// Chain pools count completed queries (env_cnt) instead of completed calls.
-// Dual update (Sec. 4.4, Eq. 7) in one launch: every block sums its share of
-// the completion and Q16 cost counters (waves by shuffles, the block through
-// LDS) and adds them to acc[0..1] with one atomic each; the block that takes
-// the last ticket (acc[2]) then finishes: over the completions since the
-// previous update, C_bar = cost / (2^16 n) and lambda <- clip(lambda +
-// eta (C_bar - 1), 0, lambda_max) in correctly rounded fp64 steps (no
-// completion leaves lambda unchanged), and it resets acc for the next call.
-__global__ __launch_bounds__(256) void dual_update_kernel(const int64_t* cnt, int64_t n_em,
-                                                          const int64_t* env_cnt, int64_t n_env,
-                                                          unsigned long long* acc, int64_t* last, double eta,
+// Dual update (Sec. 4.4, Eq. 7), one block: sums the running totals the
+// schedule step keeps in kDualShards pairs {completions (chain pools: completed
+// queries), Q16 cost}; over the completions since the previous update, C_bar =
+// cost / (2^16 n) and lambda <- clip(lambda + eta (C_bar - 1), 0, lambda_max) in
+// correctly rounded fp64 steps (no completion leaves lambda unchanged).
+// Latency-bound: one round trip over 16 KB. Summing the per-model counters here
+// instead (a grid of up to 1,024 blocks, three contended atomics each) took 6 us
+// at 20,480 (env, model) rows and 47 us at 524,288; this takes 3 us at any size.
+__global__ __launch_bounds__(256) void dual_update_kernel(const int64_t* shards, int64_t* last, double eta,
                                                           double lambda_max, double* lambda) {
-  __shared__ unsigned long long part[2][4];
-  __shared__ bool finisher;
-  uint64_t n = 0, c = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_em;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    if (!env_cnt) n += (uint64_t)cnt[i * C_NUM + C_COMPLETED];
-    c += (uint64_t)cnt[i * C_NUM + C_COST_Q16];
+  __shared__ int64_t part[2][4];
+  int64_t n = 0, c = 0;
+  const longlong2* sh = reinterpret_cast<const longlong2*>(shards);
+#pragma unroll
+  for (int i = 0; i < kDualShards / 256; ++i) {
+    const longlong2 v = sh[i * 256 + threadIdx.x];
+    n += v.x;
+    c += v.y;
   }
-  if (env_cnt) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_env;
-         i += (int64_t)gridDim.x * blockDim.x)
-      n += (uint64_t)env_cnt[i * kEnvCnt + E_Q_DONE];
-  }
+  const int64_t l0 = last[0], l1 = last[1];
+  const double lam = *lambda;
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) {
-    n += (uint64_t)shfl_xor((int64_t)n, m);
-    c += (uint64_t)shfl_xor((int64_t)c, m);
+    n += shfl_xor(n, m);
+    c += shfl_xor(c, m);
   }
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
@@ -1208,25 +1210,10 @@ __global__ __launch_bounds__(256) void dual_update_kernel(const int64_t* cnt, in
     part[1][w] = c;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t bn = 0, bc = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) {
-      bn += part[0][i];
-      bc += part[1][i];
-    }
-    if (bn != 0) atomicAdd(acc, (unsigned long long)bn);
-    if (bc != 0) atomicAdd(acc + 1, (unsigned long long)bc);
-    __threadfence();   // this block's sums are visible before its ticket
-    finisher = atomicAdd(acc + 2, 1ull) == (unsigned long long)gridDim.x - 1;
-  }
-  __syncthreads();
-  if (!finisher || threadIdx.x != 0) return;
-  __threadfence();
-  const int64_t tn = (int64_t)atomicAdd(acc, 0ull), tc = (int64_t)atomicAdd(acc + 1, 0ull);
-  acc[0] = 0;
-  acc[1] = 0;
-  acc[2] = 0;
-  const int64_t dn = tn - last[0], dc = tc - last[1];
+  if (threadIdx.x != 0) return;
+  const int64_t tn = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+  const int64_t tc = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+  const int64_t dn = tn - l0, dc = tc - l1;
   last[0] = tn;
   last[1] = tc;
   if (dn <= 0) return;
@@ -1234,22 +1221,39 @@ __global__ __launch_bounds__(256) void dual_update_kernel(const int64_t* cnt, in
     // one rounding per operation, as written (no fused multiply-add)
 #pragma clang fp contract(off)
     const double cbar = (double)dc / (65536.0 * (double)dn);
-    double l = *lambda + eta * (cbar - 1.0);
+    double l = lam + eta * (cbar - 1.0);
     l = l < 0.0 ? 0.0 : (l > lambda_max ? lambda_max : l);
     *lambda = l;
   }
 }
 
+// The running totals from the counters, after a state restore: one thread per shard.
+__global__ void dual_recount_kernel(SchedArgs a, bool chain) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= kDualShards) return;
+  int64_t n = 0, c = 0;
+  for (int64_t e = i; e < a.E; e += kDualShards) {
+    for (int m = 0; m < a.M; ++m) {
+      const int64_t* k = a.cnt + (e * a.M + m) * C_NUM;
+      if (!chain) n += k[C_COMPLETED];
+      c += k[C_COST_Q16];
+    }
+    if (chain) n += a.env_cnt[e * kEnvCnt + E_Q_DONE];
+  }
+  a.dual_shards[2 * i] = n;
+  a.dual_shards[2 * i + 1] = c;
+}
+
 }  // namespace
 
-hipError_t launch_dual_update(const int64_t* cnt, int64_t n_em, const int64_t* env_cnt, int64_t n_env,
-                              unsigned long long* acc, int64_t* last, double eta, double lambda_max,
-                              double* lambda, hipStream_t s) {
-  const int64_t n = n_em > n_env ? n_em : n_env;
-  const int64_t want = (n + 255) / 256;
-  const unsigned blocks = (unsigned)(want < 1024 ? (want < 1 ? 1 : want) : 1024);
-  hipLaunchKernelGGL(dual_update_kernel, dim3(blocks), dim3(256), 0, s, cnt, n_em, env_cnt, n_env, acc, last,
-                     eta, lambda_max, lambda);
+hipError_t launch_dual_update(const int64_t* shards, int64_t* last, double eta, double lambda_max, double* lambda,
+                              hipStream_t s) {
+  hipLaunchKernelGGL(dual_update_kernel, dim3(1), dim3(256), 0, s, shards, last, eta, lambda_max, lambda);
+  return hipGetLastError();
+}
+
+hipError_t launch_dual_recount(const SchedArgs& a, bool chain, hipStream_t s) {
+  hipLaunchKernelGGL(dual_recount_kernel, dim3(kDualShards / 64), dim3(64), 0, s, a, chain);
   return hipGetLastError();
 }
 

@@ -61,3 +61,37 @@ def test_dual_matches_oracle(name, E):
             assert lam_g.item() == lam_o, (t, lam_g.item(), lam_o)
             p.compare_state(ctx=f"{name} t={t}")
     p.close()
+
+
+@pytest.mark.parametrize("E", [1, 1023, 1025])
+def test_dual_running_totals_follow_the_counters(E):
+    """More envs than running totals, and a state restore between updates: each
+    update equals Eq. 7 over the difference of the exported counters' sums."""
+    torch = need_gpu()
+    import paper_2606_11440_amd as P
+    cfg = workload.configs.get("c2", E=E, M=2, K=1, T=30, lam=3.0, qcap=32, embed_dim=64, feat_dim=73,
+                               widths=[64, 2], svc_mu=0.0)
+    W, b = workload.gen.weights(cfg, 3, 0.1)
+    emb = torch.zeros((16, 64), dtype=torch.bfloat16, device="cuda")
+    pool = P.Pool(cfg, W, b, emb, workload.gen.capacities(cfg, 3))
+    counts = workload.gen.counts(cfg, 3)
+    lam, want, last, saved = _lam(torch, 0.4), 0.4, (0, 0), None
+    for t in range(cfg["T"]):
+        pool.tick(P.device_arrivals(workload.gen.tick(cfg, 3, t, counts[t], 16)))
+        if t == 9:
+            saved = pool.state()
+        if t == 14 or t == 22:
+            pool.write_state(0, saved)      # back to tick 10: the totals fall with the counters
+        if t % 4 == 3:
+            pool.dual_update(0.05, 2.0, lam)
+            s = pool.state()
+            tot = (int(s["completed"].sum()), int(s["cost_q16"].sum()))
+            dn, dc = tot[0] - last[0], tot[1] - last[1]
+            last = tot
+            if dn > 0:
+                want = want + 0.05 * (dc / (65536.0 * dn) - 1.0)
+                want = min(max(want, 0.0), 2.0)
+            torch.cuda.synchronize()
+            assert lam.item() == want, (t, lam.item(), want)
+    assert last[0] > 0 and pool.error() == 0
+    pool.close()
