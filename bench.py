@@ -469,7 +469,7 @@ def main():
         # and its HBM time at nominal peaks
         rbytes = np.mean([algorithmic_bytes_route(cfg, n, args.sample) for n in n_req[W_:W_ + K]])
         kname = ("route_sample_" if args.sample else "route_dual_" if cfg.get("net") == "dual" else "route_") + cfg["dtype"]
-        traffic = load_traffic("route", tag, source_hash("route.hip", "route_dev.h"))
+        traffic = load_traffic("route", tag, source_hash("route.hip", "route_dev.h", "route_split.h"))
         if flops / (peak_f * 1e12) >= rbytes / (PEAK_HBM_GBS * 1e9):
             achieved = flops / (route_avg * 1e-3) / 1e12
             return {"kernel": kname, "bound": "mfma", "achieved": achieved,

@@ -146,15 +146,24 @@ def _check(status, pool=None):
     return status
 
 
+_current = None   # torch's (raw stream of a device, current device) accessors
+
+
 def _stream(stream):
-    if stream is None:
+    """The handle of `stream`, or of torch's current stream on the current
+    device (its raw handle: building the Stream object costs more than a launch)."""
+    if stream is not None:
+        return int(stream)
+    global _current
+    if _current is None:
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        torch.cuda.init()
+        _current = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    return _current[0](_current[1]())
 
 
 def _dptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _hptr(a):
@@ -236,34 +245,45 @@ def im_pool_create_dual(desc: ImPoolDesc, params: dict, roles, emb, n_queries: i
 
 
 def im_route(pool, arr: ImArrivals, actions, logits=None, stream=None):
-    _check(load().im_route(pool, ctypes.byref(arr), _dptr(actions), _dptr(logits),
-                           _stream(stream)), pool)
+    st = (_lib or load()).im_route(pool, arr, _dptr(actions), _dptr(logits), _stream(stream))
+    if st:
+        _check(st, pool)
 
 
 def im_route_sample(pool, arr: ImArrivals, seed: int, greedy: bool, actions, logp=None,
                     entropy=None, value=None, logits=None, stream=None):
     """RL-rollout route: device tensors for the outputs (None to skip)."""
     out = ImPolicyOut(_dptr(actions), _dptr(logp), _dptr(entropy), _dptr(value), _dptr(logits))
-    _check(load().im_route_sample(pool, ctypes.byref(arr), int(seed) & 0xffffffffffffffff,
-                                  int(bool(greedy)), ctypes.byref(out), _stream(stream)), pool)
+    st = (_lib or load()).im_route_sample(pool, arr, int(seed) & 0xffffffffffffffff, 1 if greedy else 0, out,
+                                          _stream(stream))
+    if st:
+        _check(st, pool)
 
 
 def im_schedule(pool, arr: ImArrivals, actions, stream=None):
-    _check(load().im_schedule(pool, ctypes.byref(arr), _dptr(actions), _stream(stream)), pool)
+    st = (_lib or load()).im_schedule(pool, arr, _dptr(actions), _stream(stream))
+    if st:
+        _check(st, pool)
 
 
 def im_tick(pool, arr: ImArrivals, actions_out=None, stream=None):
-    _check(load().im_tick(pool, ctypes.byref(arr), _dptr(actions_out), _stream(stream)), pool)
+    st = (_lib or load()).im_tick(pool, arr, _dptr(actions_out), _stream(stream))
+    if st:
+        _check(st, pool)
 
 
 def im_tick_noalloc(pool, arr: ImArrivals, stream=None):
     """im_tick with the actions staged in the library's static device array."""
-    _check(load().im_tick_noalloc(pool, ctypes.byref(arr), _stream(stream)), pool)
+    st = (_lib or load()).im_tick_noalloc(pool, arr, _stream(stream))
+    if st:
+        _check(st, pool)
 
 
 def im_dual_update(pool, eta: float, lambda_max: float, lam, stream=None):
     """Eq. 7 on the device; `lam` is a device float64 tensor [1] (in/out)."""
-    _check(load().im_dual_update(pool, float(eta), float(lambda_max), _dptr(lam), _stream(stream)), pool)
+    st = (_lib or load()).im_dual_update(pool, float(eta), float(lambda_max), _dptr(lam), _stream(stream))
+    if st:
+        _check(st, pool)
 
 
 _hip = None

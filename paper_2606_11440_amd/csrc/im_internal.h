@@ -190,9 +190,6 @@ hipError_t launch_dual_update(const int64_t* shards, int64_t* last, double eta, 
 hipError_t launch_dual_recount(const SchedArgs& a, bool chain, hipStream_t s);
 bool route_supported(int dtype, int hidden, int n_layers, int out_tiles);
 bool dual_supported(int embed_dim, int out_rows);
-// bf16 MLP policies of any shape, features split over a block's waves (route_split.hip).
-bool split_supported(int hidden);
-hipError_t launch_split(const RouteArgs& a, int hidden, int n_layers, int out_tiles, hipStream_t s);
 // Role projections of the dual-pathway executor: out[r][tile][g][16] =
 // b_sem + W_sem[:, E_d:] e_r in fp32 for every role r (bf16 inputs).
 //   w_role [128 x E_d] bf16 bits, roles [n_roles x E_d] bf16 bits, b_sem [128]

@@ -17,6 +17,7 @@
 // rounded to bf16 after the ReLU); fp32 pools use v_mfma_f32_16x16x4_f32 on
 // 16-row tiles in the same transposed scheme.
 #include "route_dev.h"
+#include "route_split.h"
 
 namespace im {
 namespace {
@@ -1158,8 +1159,6 @@ __global__ void role_projection_kernel(const uint16_t* w_role, const uint16_t* r
   const int T = o >> 5, w = o & 31, v = ((w >> 3) << 2) | (w & 3), g = (w >> 2) & 1;
   out[(((size_t)r * 4 + T) * 2 + g) * 16 + v] = acc;
 }
-
-typedef void (*RouteKernel)(RouteArgs);
 
 template <int H, int NL, int NR>
 RouteKernel pick_f32s(int at) {

@@ -12,6 +12,7 @@
 //
 // Sums run in the order of the persistent kernels (bias first, K ascending),
 // so the logits are the same bit for bit.
+#pragma once
 #include "route_dev.h"
 
 namespace im {
@@ -275,8 +276,6 @@ SplitLaunch pick_nl(int nl, int at, int size) {
   return nl == 2 ? pick_rows<H, 2>(at, size) : pick_rows<H, 3>(at, size);
 }
 
-}  // namespace
-
 bool split_supported(int hidden) {
   return hidden == 32 || hidden == 64 || hidden == 128 || hidden == 256 || hidden == 512;
 }
@@ -310,4 +309,5 @@ hipError_t launch_split(const RouteArgs& a, int hidden, int n_layers, int out_ti
   return hipGetLastError();
 }
 
+}  // namespace
 }  // namespace im
