@@ -379,7 +379,7 @@ def im_read_state(pool, env_begin: int, env_count: int, M: int, A: int, S: int, 
     envs = np.zeros(E, ENV_DT)
     models = np.zeros(E * M, MODEL_DT)
     slots = np.zeros(E * M * S, SLOT_DT)
-    queues = np.zeros(E * M * (qcap if with_queues else 1), ENTRY_DT)
+    queues = np.empty(E * M * (qcap if with_queues else 1), ENTRY_DT)
     hist = np.zeros(E * A, np.int64)
     tick = ctypes.c_int32(0)
     _check(load().im_read_state(pool, env_begin, env_count, ctypes.byref(tick), _hptr(envs),
@@ -388,9 +388,11 @@ def im_read_state(pool, env_begin: int, env_count: int, M: int, A: int, S: int, 
     md = models.reshape(E, M)
     qarr = None
     if with_queues:
-        q = queues.reshape(E, M, qcap)
-        qarr = np.stack([q["key"], q["id"], q["t_arr"], q["svc"].astype(np.int32),
-                         q["budget"].astype(np.int32)], axis=-1).astype(np.int32)
+        w = queues.view(np.int32).reshape(E, M, qcap, 4)   # key, id, t_arr, svc | budget << 16
+        qarr = np.empty((E, M, qcap, 5), np.int32)
+        qarr[..., :3] = w[..., :3]
+        np.bitwise_and(w[..., 3], 0xffff, out=qarr[..., 3])
+        np.right_shift(w[..., 3], 16, out=qarr[..., 4])
     sl = slots.reshape(E, M, S)
     sarr = np.stack([sl["id"], sl["t_arr"], sl["rem"], sl["budget"]], axis=-1).astype(np.int32)
     out = dict(t=int(tick.value), next_id=envs["next_id"].copy(), arrived=envs["arrived"].copy(),

@@ -64,6 +64,8 @@ struct im_pool {
   int32_t cu_count = 0;
   int32_t route_blocks = -1;   // grid of the persistent route kernels (-1: one block per CU; 0: none)
   int32_t sched_waves = 4;     // envs per block of the schedule kernel
+  void* stage = nullptr;       // pinned staging of state exports (at most kExportBytes; from the first export on)
+  size_t stage_bytes = 0;
   int32_t* scratch = nullptr;  // this device's static actions staging (im_tick_noalloc)
   bool rpm_active = false;   // some model was given a rate limit (the windows are tracked from then on)
   std::string last_error;
@@ -162,6 +164,125 @@ __global__ void set_rpm_kernel(ModelRec* r, int32_t limit, float inv) {
   r->inv_rpm = inv;
 }
 
+// ---- state export ----------------------------------------------------------
+// One block per (env, model) row writes that row's part of a state snapshot in
+// the host layouts of inframind.h straight into pinned host memory, the queue in
+// service order: the sorted front, then the pool, sorted here in LDS (a bitonic
+// network over the next power of two; every pool key exceeds every front key).
+// A pool of more than kExportSort entries goes out unsorted and is sorted on the
+// host. Reading 16 envs x 5 models x 256 entries: seven copies and 80 host sorts
+// took 500 us, this takes 60 (bound by the two synchronisations and the stores
+// over PCIe).
+constexpr int kExportSort = 4096;                  // 64 KB of LDS
+constexpr size_t kExportBytes = size_t(4) << 20;   // pinned staging: a larger range goes in several launches
+
+struct ExportArgs {
+  const ModelRec* ms;
+  const int64_t* cnt;
+  const int64_t* env_cnt;
+  const int64_t* hist;
+  const int4* slots;
+  const int4* front;
+  const int4* pool;
+  const uint8_t* ring;
+  int32_t M, S, A, qcap;
+  int64_t em0;           // first (env, model) row of the launch; its outputs start at their pointers
+  const ModelRec* first; // first record of the exported range: the tick the rate-limit history counts from
+  int32_t* tick;         // outputs; NULL: skipped
+  im_env_state* envs;
+  im_model_state* models;
+  im_slot* slots_out;
+  int4* queues;          // im_entry has the device entry's layout
+  int2* fp;              // with queues: front and pool entries of the row
+  int64_t* hist_out;
+};
+static_assert(sizeof(im_entry) == sizeof(int4), "an exported entry is a device entry");
+
+__device__ __forceinline__ bool entry_less(const int4& x, const int4& y) {
+  return x.x != y.x ? x.x < y.x : x.y < y.y;
+}
+
+__global__ __launch_bounds__(256) void export_kernel(ExportArgs a) {
+  __shared__ int4 q[kExportSort];
+  const int tid = threadIdx.x;
+  const int64_t i = blockIdx.x;                                  // row of the launch
+  const int64_t em = a.em0 + i;
+  const int64_t e = em / a.M;
+  const int64_t el = e - a.em0 / a.M;                            // env of the launch
+  const int m = (int)(em - e * a.M);
+  const ModelRec r = a.ms[em];
+  const ModelRec& r0 = a.ms[em - m];                             // the env's first record: its tick and next id
+  const int32_t t = r0.t;
+  if (i == 0 && tid == 0 && a.tick) *a.tick = t;
+  if (a.envs && m == 0 && tid == 0) {
+    const int64_t* c = a.env_cnt + e * im::kEnvCnt;
+    im_env_state o{};
+    o.arrived = c[im::E_ARRIVED];
+    o.rej_nomodel = c[im::E_REJ_NOMODEL];
+    o.next_id = r0.next_id;
+    o.q_done = c[im::E_Q_DONE];
+    o.q_met = c[im::E_Q_MET];
+    a.envs[el] = o;
+  }
+  if (a.hist_out && m == 0)
+    for (int j = tid; j < a.A; j += 256) a.hist_out[el * a.A + j] = a.hist[e * a.A + j];
+  if (a.models) {
+    if (tid < im::kRpmWindow) {   // the ring in ticks before the last completed one
+      const int64_t tau = (int64_t)a.first->t - 1 - tid;
+      a.models[i].rpm_hist[tid] = tau >= 0 ? a.ring[em * im::kRpmRing + tau % im::kRpmWindow] : 0;
+    }
+    if (tid == 64) {
+      im_model_state& o = a.models[i];
+      const int64_t* c = a.cnt + em * im::C_NUM;
+      o.qlen = r.qlen; o.busy = r.busy; o.ewma_q8 = r.ewma; o.backlog = r.backlog;
+      o.capacity = r.cap; o.enabled = r.enabled; o._pad0 = 0; o._pad1 = 0;
+      o.rej_overflow = c[im::C_REJ_OVERFLOW]; o.enqueued = c[im::C_ENQUEUED];
+      o.started = c[im::C_STARTED]; o.completed = c[im::C_COMPLETED]; o.slo_met = c[im::C_SLO_MET];
+      o.lat_sum = c[im::C_LAT_SUM]; o.wait_sum = c[im::C_WAIT_SUM]; o.cost_q16 = c[im::C_COST_Q16];
+      o.rpm_limit = r.rpm_limit; o.rpm_count = r.rpm_count; o._pad2 = 0;
+    }
+  }
+  if (a.slots_out && tid < a.S) {
+    // the device keeps a busy slot's completion tick; the state reports the
+    // service ticks left after the env's last completed tick
+    const int4 v = a.slots[em * a.S + tid];
+    im_slot o{-1, 0, 0, 0};
+    if (v.x >= 0) o = im_slot{v.x, v.y, v.z - t + 1, v.w};
+    a.slots_out[i * a.S + tid] = o;
+  }
+  if (!a.queues) return;
+  int4* out = a.queues + i * a.qcap;
+  const int4* front = a.front + em * im::kFront + r.fh;
+  const int4* pool = a.pool + em * (int64_t)a.qcap;
+  const int fn = r.fn, P = r.P, n = min(fn + P, a.qcap);
+  if (tid == 0) a.fp[i] = make_int2(fn, P);
+  for (int j = tid; j < a.qcap; j += 256) {
+    if (j < fn) out[j] = front[j];
+    else if (j >= n) out[j] = make_int4(0, 0, 0, 0);
+    else if (P > kExportSort) out[j] = pool[j - fn];
+  }
+  if (P > kExportSort) return;   // uniform
+  int n2 = 1;
+  while (n2 < P) n2 *= 2;
+  for (int j = tid; j < n2; j += 256)
+    q[j] = j < P ? pool[j] : make_int4(0x7fffffff, 0x7fffffff, 0, 0);
+  for (int k = 2; k <= n2; k *= 2) {
+    for (int s = k / 2; s > 0; s /= 2) {
+      __syncthreads();
+      for (int j = tid; j < n2 / 2; j += 256) {
+        const int lo = 2 * j - (j & (s - 1)), hi = lo + s;   // pairs at distance s
+        const int4 x = q[lo], y = q[hi];
+        if (entry_less(y, x) == ((lo & k) == 0)) {
+          q[lo] = y;
+          q[hi] = x;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (int j = tid; fn + j < n; j += 256) out[fn + j] = q[j];
+}
+
 // Ring byte of tick tau (the device keeps the dispatches of tick tau at tau % 60).
 inline int rpm_slot(int64_t tau) { return (int)(((tau % im::kRpmWindow) + im::kRpmWindow) % im::kRpmWindow); }
 
@@ -190,6 +311,7 @@ void free_pool(im_pool* p) {
                   p->rpm_ring, p->W_res, p->dual_p, p->pend, p->pcnt, p->front_ext,
                   p->pool_ext, p->slot_ext, p->roff, p->n_rows, p->rq, p->rb, p->rr};
   for (void* b : bufs) if (b) (void)hipFree(b);
+  if (p->stage) (void)hipHostFree(p->stage);
   delete p;
 }
 
@@ -839,94 +961,80 @@ im_status im_read_state(im_pool* p, int32_t env_begin, int32_t env_count, int32_
     return fail(p, IM_EINVAL, "env range out of bounds");
   IM_HIP(p, hipDeviceSynchronize());
   const int M = p->d.n_models, S = p->S, qcap = p->d.queue_cap, A = p->A;
-  const size_t em0 = (size_t)env_begin * M, EMc = (size_t)env_count * M;
-  std::vector<ModelRec> recs(EMc);
-  std::vector<int64_t> cnt(EMc * im::C_NUM);
-  if (EMc) {
-    IM_HIP(p, hipMemcpy(recs.data(), p->ms + em0, EMc * sizeof(ModelRec), hipMemcpyDeviceToHost));
-    IM_HIP(p, hipMemcpy(cnt.data(), p->cnt + em0 * im::C_NUM, cnt.size() * 8, hipMemcpyDeviceToHost));
-    p->t = recs[0].t;   // every env advances every tick; graph replays advance it too
+  if (env_count == 0) {
+    if (tick) *tick = p->t;
+    return IM_OK;
+  }
+  const size_t row_queue = (size_t)qcap * sizeof(im_entry) + sizeof(int2);
+  const size_t env_rest = sizeof(im_env_state) + M * (sizeof(im_model_state) + S * sizeof(im_slot)) + A * sizeof(int64_t);
+  const int64_t em_begin = (int64_t)env_begin * M, rows = (int64_t)env_count * M;
+  constexpr size_t kPad = 8 * 64;              // the parts start at multiples of 64 bytes
+  constexpr size_t room = kExportBytes - kPad;
+  const size_t all = env_count * (env_rest + (queues ? M * row_queue : 0));
+  const size_t want = kPad + std::min(all, room);
+  if (p->stage_bytes < want) {
+    if (p->stage) IM_HIP(p, hipHostFree(p->stage));
+    p->stage = nullptr;
+    p->stage_bytes = 0;
+    IM_HIP(p, hipHostMalloc(&p->stage, want, hipHostMallocDefault));
+    p->stage_bytes = want;
+  }
+  // Rows [em0, em0 + n) of the range: everything but the queues (rest, whole
+  // envs) and/or the queues, in one launch.
+  auto part_of = [&](int64_t em0, int64_t n, bool rest, bool queue) -> hipError_t {
+    const int64_t ne = n / M, at_row = em0 - em_begin, at_env = at_row / M;
+    ExportArgs a{};
+    a.ms = p->ms; a.cnt = p->cnt; a.env_cnt = p->env_cnt; a.hist = p->hist; a.slots = p->slots;
+    a.front = p->front; a.pool = p->qpool; a.ring = p->rpm_ring;
+    a.M = M; a.S = S; a.A = A; a.qcap = qcap;
+    a.em0 = em0;
+    a.first = p->ms + em_begin;
+    char* at = static_cast<char*>(p->stage);
+    auto take = [&](size_t bytes) {
+      char* x = at;
+      at += (bytes + 63) & ~size_t(63);
+      return x;
+    };
+    a.tick = reinterpret_cast<int32_t*>(take(sizeof(int32_t)));
+    if (rest && envs) a.envs = reinterpret_cast<im_env_state*>(take(ne * sizeof(im_env_state)));
+    if (rest && models) a.models = reinterpret_cast<im_model_state*>(take(n * sizeof(im_model_state)));
+    if (rest && slots) a.slots_out = reinterpret_cast<im_slot*>(take(n * S * sizeof(im_slot)));
+    if (rest && hist) a.hist_out = reinterpret_cast<int64_t*>(take(ne * A * sizeof(int64_t)));
+    if (queue) {
+      a.queues = reinterpret_cast<int4*>(take(n * qcap * sizeof(im_entry)));
+      a.fp = reinterpret_cast<int2*>(take(n * sizeof(int2)));
+    }
+    hipLaunchKernelGGL(export_kernel, dim3((unsigned)n), dim3(256), 0, nullptr, a);
+    hipError_t err = hipGetLastError();
+    if (err == hipSuccess) err = hipStreamSynchronize(nullptr);
+    if (err != hipSuccess) return err;
+    if (at_row == 0) p->t = *a.tick;   // every env advances every tick; graph replays advance it too
+    if (a.envs) std::memcpy(envs + at_env, a.envs, ne * sizeof(im_env_state));
+    if (a.models) std::memcpy(models + at_row, a.models, n * sizeof(im_model_state));
+    if (a.slots_out) std::memcpy(slots + at_row * S, a.slots_out, n * S * sizeof(im_slot));
+    if (a.hist_out) std::memcpy(hist + at_env * A, a.hist_out, ne * A * sizeof(int64_t));
+    if (queue) {
+      std::memcpy(queues + at_row * qcap, a.queues, n * qcap * sizeof(im_entry));
+      for (int64_t i = 0; i < n; ++i) {
+        if (a.fp[i].y <= kExportSort) continue;
+        im_entry* q = queues + (at_row + i) * qcap;
+        std::sort(q + a.fp[i].x, q + std::min(a.fp[i].x + a.fp[i].y, qcap), [](const im_entry& x, const im_entry& y) {
+          return x.key != y.key ? x.key < y.key : x.id < y.id;
+        });
+      }
+    }
+    return hipSuccess;
+  };
+  if (all <= room) {
+    IM_HIP(p, part_of(em_begin, rows, true, queues != nullptr));
+  } else {
+    const int64_t per = (int64_t)std::max<size_t>(1, room / env_rest) * M;
+    for (int64_t r = 0; r < rows; r += per) IM_HIP(p, part_of(em_begin + r, std::min(per, rows - r), true, false));
+    const int64_t per_q = (int64_t)std::max<size_t>(1, room / row_queue);
+    for (int64_t r = 0; queues && r < rows; r += per_q)
+      IM_HIP(p, part_of(em_begin + r, std::min(per_q, rows - r), false, true));
   }
   if (tick) *tick = p->t;
-  if (envs && env_count) {
-    constexpr int EC = im::kEnvCnt;
-    std::vector<int64_t> ec((size_t)env_count * EC);
-    IM_HIP(p, hipMemcpy(ec.data(), p->env_cnt + (size_t)env_begin * EC, ec.size() * 8,
-                        hipMemcpyDeviceToHost));
-    for (int e = 0; e < env_count; ++e) {
-      envs[e].arrived = ec[EC * e + im::E_ARRIVED];
-      envs[e].rej_nomodel = ec[EC * e + im::E_REJ_NOMODEL];
-      envs[e].next_id = recs[(size_t)e * M].next_id;
-      envs[e]._pad = 0;
-      envs[e].q_done = ec[EC * e + im::E_Q_DONE];
-      envs[e].q_met = ec[EC * e + im::E_Q_MET];
-    }
-  }
-  if (models) {
-    for (size_t i = 0; i < EMc; ++i) {
-      im_model_state& o = models[i];
-      std::memset(&o, 0, sizeof(o));
-      o.qlen = recs[i].qlen; o.busy = recs[i].busy; o.ewma_q8 = recs[i].ewma;
-      o.backlog = recs[i].backlog; o.capacity = recs[i].cap; o.enabled = recs[i].enabled;
-      const int64_t* c = &cnt[i * im::C_NUM];
-      o.rej_overflow = c[im::C_REJ_OVERFLOW]; o.enqueued = c[im::C_ENQUEUED];
-      o.started = c[im::C_STARTED]; o.completed = c[im::C_COMPLETED]; o.slo_met = c[im::C_SLO_MET];
-      o.lat_sum = c[im::C_LAT_SUM]; o.wait_sum = c[im::C_WAIT_SUM];
-      o.cost_q16 = c[im::C_COST_Q16];
-      o.rpm_limit = recs[i].rpm_limit;
-      o.rpm_count = recs[i].rpm_count;
-    }
-    std::vector<uint8_t> ring(EMc * im::kRpmRing);
-    if (EMc)
-      IM_HIP(p, hipMemcpy(ring.data(), p->rpm_ring + em0 * im::kRpmRing, ring.size(), hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < EMc; ++i)
-      for (int k = 0; k < im::kRpmWindow; ++k)
-        models[i].rpm_hist[k] = (int64_t)p->t - 1 - k >= 0 ? ring[i * im::kRpmRing + rpm_slot((int64_t)p->t - 1 - k)] : 0;
-  }
-  if (slots && EMc) {
-    // The device keeps a busy slot's completion tick; the state reports the
-    // service ticks left after the env's last completed tick.
-    std::vector<int4> sl(EMc * S);
-    IM_HIP(p, hipMemcpy(sl.data(), p->slots + em0 * S, sl.size() * sizeof(int4), hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < EMc; ++i) {
-      const int32_t t_env = recs[(i / M) * M].t;
-      for (int s = 0; s < S; ++s) {
-        const int4 v = sl[i * S + s];
-        im_slot& o = slots[i * S + s];
-        if (v.x >= 0) { o.id = v.x; o.t_arr = v.y; o.rem = v.z - t_env + 1; o.budget = v.w; }
-        else { o.id = -1; o.t_arr = 0; o.rem = 0; o.budget = 0; }
-      }
-    }
-  }
-  if (hist && env_count)
-    IM_HIP(p, hipMemcpy(hist, p->hist + (size_t)env_begin * A, (size_t)env_count * A * 8,
-                        hipMemcpyDeviceToHost));
-  if (queues && EMc) {
-    // Materialise each queue in service order: the sorted front, then the
-    // pool sorted by (key, id) (every pool key exceeds every front key).
-    std::vector<int4> fr(EMc * im::kFront), pl(EMc * (size_t)qcap);
-    IM_HIP(p, hipMemcpy(fr.data(), p->front + em0 * im::kFront, fr.size() * sizeof(int4),
-                        hipMemcpyDeviceToHost));
-    IM_HIP(p, hipMemcpy(pl.data(), p->qpool + em0 * qcap, pl.size() * sizeof(int4),
-                        hipMemcpyDeviceToHost));
-    std::memset(queues, 0, EMc * qcap * sizeof(im_entry));
-    std::vector<int4> tmp;
-    for (size_t i = 0; i < EMc; ++i) {
-      const ModelRec& r = recs[i];
-      tmp.assign(fr.begin() + i * im::kFront + r.fh, fr.begin() + i * im::kFront + r.fh + r.fn);
-      const size_t f = tmp.size();
-      tmp.insert(tmp.end(), pl.begin() + i * qcap, pl.begin() + i * qcap + r.P);
-      std::sort(tmp.begin() + f, tmp.end(), [](const int4& x, const int4& y) {
-        return x.x != y.x ? x.x < y.x : x.y < y.y;
-      });
-      im_entry* q = queues + i * qcap;
-      for (size_t k = 0; k < tmp.size() && k < (size_t)qcap; ++k) {
-        q[k].key = tmp[k].x; q[k].id = tmp[k].y; q[k].t_arr = tmp[k].z;
-        q[k].svc = (uint16_t)(tmp[k].w & 0xffff);
-        q[k].budget = (int16_t)(tmp[k].w >> 16);
-      }
-    }
-  }
   return IM_OK;
 }
 
