@@ -130,23 +130,27 @@ __device__ __forceinline__ void merge_front(Queue& q, int4& fe, int2& fx, const 
   if constexpr (CHAIN) fx = lane < keep ? make_int2(plo[1], plo[2]) : make_int2(0, 0);
 }
 
+// Chunks of 64 pool keys a refill has in flight, and the candidates its LDS
+// list has room for.
+constexpr int kScanChunks = 8;
+constexpr int kCandidates = 1024;
+
 // Refill the (empty) front with the min(64, P) smallest pool entries; the new
 // front is returned in `fe` (lane i: entry i), the front array is not written.
-// `pk`/`pi` are this wave's LDS staging rows (64 keys, 64 pool indices), `kb`
-// its LDS buffer for 4 chunks of pool keys.
-// Pool chunks (of 64 entries) per round of the refill scan (chain pools,
-// whose kernel holds more LDS, use fewer to keep 4 blocks per CU), and the
-// s_waitcnt immediate (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt
-// 6:4 and lgkmcnt 11:8 left at their maxima) that waits until at most n
-// vector-memory operations of this wave are outstanding (n < 16).
-template <bool CHAIN>
-constexpr int refill_chunks() { return CHAIN ? 2 : 4; }
-constexpr int wait_vm(int n) { return 0x0F70 | n; }
-
+// `cand` is this wave's LDS list of candidate pool indices.
 // With CHAIN the chain words move along: `fx`, `pool_ext`.
+//
+// A launch lasts as long as its slowest envs, which are those that refill, so
+// one wave's latency counts. Sixty-four keys sampled across the pool give a
+// threshold that about 190 of 2,000 keys do not exceed; a scan of the keys alone
+// (registers, 8 chunks in flight) lists those, and only they are sorted, 64 at a
+// time; a pool of up to 256 entries is sorted whole. Merging every candidate
+// below a running threshold that started at the first chunk's maximum, over LDS
+// copies of keys and ids, took five sorts and eight rounds (9 us of scanning a
+// refill, now 4). schedule_kernel with queues of 2,048 full, 4,096 envs of 64
+// requests: 30.8 -> 25.2 us; chains 29.5 -> 24.4; queues of 256: 21.9 -> 22.4.
 template <bool CHAIN>
-__device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext, int64_t* pk,
-                       int32_t* pi, int2* kb, int key_mode) {
+__device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext, int32_t* cand, int key_mode) {
   const int lane = lane_id();
   const int P = q.P;
   wave_mem_sync();   // this tick's pool appends are read below
@@ -176,87 +180,88 @@ __device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext,
     q.P = 0;
     return;
   }
-  // Top-64 selection. `ck`/`idx` hold the 64 smallest keys seen so far,
-  // ascending across lanes; thr is the largest of them. Later pool entries
-  // below thr are collected in LDS and merged 64 at a time: a sorted batch,
-  // reversed, taken elementwise-min with the best set gives a bitonic
-  // sequence holding the 64 smallest of both, which one merge network sorts.
-  const int4 e0 = pool[lane];
-  int64_t ck = composite(e0.x, e0.y);
-  int32_t idx[1] = {lane};
-  bitonic_sort64<1>(ck, idx);
-  int64_t thr = readlane64(ck, 63);
-  int np = 0;   // candidates staged in pk/pi[0, np)
-  auto flush = [&]() {
-    int64_t bk = lane < np ? pk[lane] : kKeyMax;
-    int32_t bi[1] = {lane < np ? pi[lane] : 0};
+  // `ck`/`idx` hold the 64 smallest entries merged so far, ascending across lanes.
+  int64_t ck = kKeyMax;
+  int32_t idx[1] = {0};
+  bool some = false;   // ck holds entries
+  // Merges a batch of 64 entries (kKeyMax: none) into the best: sorted, reversed
+  // and taken elementwise-min with the best set it gives a bitonic sequence
+  // holding the 64 smallest of both, which one merge network sorts.
+  auto merge_batch = [&](int64_t bk, int32_t (&bi)[1]) {
     bitonic_sort64<1>(bk, bi);
-    const int64_t rk = shfl(bk, 63 - lane);
-    const int32_t ri = shfl(bi[0], 63 - lane);
-    if (rk < ck) { ck = rk; idx[0] = ri; }
-    bitonic_merge64<1>(ck, idx);
-    thr = readlane64(ck, 63);
-    np = 0;
-  };
-  // The keys and ids of the remaining entries come into LDS through the LDS
-  // DMA path (no registers held by loads in flight), kRefillChunks chunks of
-  // 64 entries per round, double-buffered: the next round's loads are issued
-  // before the current round is scanned. Lanes past the pool's end load its
-  // last entry (an address in bounds) and are ignored.
-  constexpr int G = refill_chunks<CHAIN>();
-  int32_t* lk = reinterpret_cast<int32_t*>(kb);   // [2][G * kFront] keys
-  int32_t* li = lk + 2 * G * kFront;              // [2][G * kFront] ids
-  const int rounds = (P - kFront + G * kFront - 1) / (G * kFront);
-  auto issue = [&](int r) {
-    const int st = r & 1;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int i = kFront + (r * G + g) * kFront + lane;
-      const int32_t* src = reinterpret_cast<const int32_t*>(pool + (i < P ? i : P - 1));
-      __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)(lk + (st * G + g) * kFront),
-                                       4, 0, 0);
-      __builtin_amdgcn_global_load_lds(src + 1, (__attribute__((address_space(3))) void*)(li + (st * G + g) * kFront),
-                                       4, 0, 0);
-    }
-  };
-  issue(0);
-  for (int r = 0; r < rounds; ++r) {
-    // vector-memory counter: wait for this round's 2G loads, keep the next round's in flight
-    if (r + 1 < rounds) {
-      issue(r + 1);
-      __builtin_amdgcn_s_waitcnt(wait_vm(2 * G));
+    if (!some) {
+      ck = bk;
+      idx[0] = bi[0];
+      some = true;
     } else {
-      __builtin_amdgcn_s_waitcnt(wait_vm(0));
+      const int64_t rk = shfl(bk, 63 - lane);
+      const int32_t ri = shfl(bi[0], 63 - lane);
+      if (rk < ck) { ck = rk; idx[0] = ri; }
+      bitonic_merge64<1>(ck, idx);
     }
-    const int st = r & 1;
+  };
+  // Entry i's key (and id) by a 32-bit byte offset from the pool, which is
+  // uniform: one address register per load.
+  auto at = [&](uint32_t i) { return reinterpret_cast<const char*>(pool) + i * 16u; };
+  auto key_at = [&](uint32_t i) { return *reinterpret_cast<const int32_t*>(at(i)); };
+  auto entry_at = [&](uint32_t i) { return *reinterpret_cast<const int2*>(at(i)); };
+  if (P <= 256) {
+    // every entry is a candidate (a threshold would save at most two sorts): all in flight at once
+    int2 e[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) e[c] = entry_at((uint32_t)min(c * 64 + lane, P - 1));
 #pragma unroll 1
-    for (int g = 0; g < G; ++g) {
-      const int i = kFront + (r * G + g) * kFront + lane;
-      // Read through inline assembly: the compiler treats an LDS read after an
-      // LDS DMA as dependent on every DMA in flight and would wait for the
-      // next round's loads too; the explicit vmcnt wait above is the exact one.
-      int32_t kv, iv;
-      const uint32_t ak = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int32_t*)(lk + (st * G + g) * kFront + lane);
-      const uint32_t ai = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int32_t*)(li + (st * G + g) * kFront + lane);
-      asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)"
-                   : "=v"(kv), "=v"(iv) : "v"(ak), "v"(ai));
-      const int64_t kc = i < P ? composite(kv, iv) : kKeyMax;
-      uint64_t cm = ballot(kc < thr);
-      if (cm == 0) continue;
-      if (np + popc64(cm) > kFront) {
-        flush();
-        cm = ballot(kc < thr);
-        if (cm == 0) continue;
+    for (int b = 0; b < P; b += 64) {
+      int32_t bi[1] = {b + lane};
+      merge_batch(b + lane < P ? composite(e[0].x, e[0].y) : kKeyMax, bi);
+      e[0] = e[1];
+      e[1] = e[2];
+      e[2] = e[3];
+    }
+  } else {
+    // The sample: entry l P / 64 in lane l (the pool keeps arrival order in
+    // stretches, so neighbours are no sample). About (j + 1) / 65 of the keys lie
+    // at or below its j-th smallest; j is chosen so that fewer than 64 do about
+    // once in 20 refills, and the next threshold is then tried on the rest.
+    int32_t sk = key_at(((uint32_t)lane * (uint32_t)P) >> 6);
+    int32_t kc[kScanChunks];   // a chunk's keys per register; lanes past the pool's end read its last entry
+#pragma unroll
+    for (int c = 0; c < kScanChunks; ++c) kc[c] = key_at((uint32_t)min(c * 64 + lane, P - 1));
+    bitonic_sort64(sk);
+    int32_t below = (int32_t)0x80000000;   // keys at or below it are already merged (no key is the lowest int)
+    int np = 0, found = 0;                 // candidates listed, and in all
+    for (int j = 5120 / P + 3; found < kFront; j = 2 * j + 4) {
+      const int32_t thr = j < 63 ? __builtin_amdgcn_readlane(sk, j) : 0x7fffffff;
+      for (int c0 = 0; c0 * 64 < P; c0 += kScanChunks) {
+#pragma unroll
+        for (int c = 0; c < kScanChunks; ++c) {
+          const int i = (c0 + c) * 64 + lane;
+          const uint64_t cm = ballot(kc[c] <= thr && kc[c] > below && i < P);
+          kc[c] = key_at((uint32_t)min(i + kScanChunks * 64, P - 1));
+          if (cm != 0) {
+            if ((cm >> lane) & 1ull) cand[np + prefix_count(cm)] = i;
+            np += popc64(cm);
+          }
+        }
+        // merge them at the pass's end, or when the next chunks might not fit the list
+        if (np > kCandidates - kScanChunks * 64 || (c0 + kScanChunks) * 64 >= P) {
+          found += np;
+          for (int b = 0; b < np; b += 64) {
+            const bool on = b + lane < np;
+            int32_t bi[1] = {on ? cand[b + lane] : 0};
+            const int2 e = entry_at((uint32_t)bi[0]);
+            merge_batch(on ? composite(e.x, e.y) : kKeyMax, bi);
+          }
+          np = 0;
+        }
       }
-      if ((cm >> lane) & 1ull) {
-        const int pos = np + prefix_count(cm);
-        pk[pos] = kc;
-        pi[pos] = i;
+      below = thr;
+      if (found < kFront) {
+#pragma unroll
+        for (int c = 0; c < kScanChunks; ++c) kc[c] = key_at((uint32_t)min(c * 64 + lane, P - 1));
       }
-      np += popc64(cm);
     }
   }
-  if (np > 0) flush();
   const int sel = idx[0];
   fe = pool[sel];
   if constexpr (CHAIN) fx = pool_ext[sel];
@@ -363,6 +368,8 @@ enum {
   MW_ND,         // earliest completion tick among the busy slots
   MW_NUM
 };
+// Rows of a wave's LDS copy of its LaneState while queues are refilled.
+enum { PK_QLEN = 0, PK_BUSY, PK_EWMA, PK_BACKLOG, PK_FH, PK_FN, PK_P, PK_MASK, PK_DONE, PK_FMK, PK_FMI, PK_CHG, PK_NUM };
 enum { MD_LAT = 0, MD_COST, MD_NUM };   // 64-bit sums: latency, Q16 cost
 
 // Adds v to a 64-bit counter without reading it back (a vector atomic whose
@@ -405,17 +412,15 @@ __device__ __forceinline__ void counter_add(int64_t* p, int64_t v) {
 // the query's deadline, to the pending list of the next tick.
 template <bool RPM, bool CHAIN, int PF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void schedule_kernel(SchedArgs a) {
-  // sorted chunks; in the service phase the refill scan's key buffer, then
-  // the counter staging
+  // sorted chunks; in the service phase the refill's candidate list, then the
+  // counter staging
   __shared__ int4 stage[4][kStageChunks * 64];
   __shared__ int2 stage_x[4][CHAIN ? kStageChunks * 64 : 1];
   __shared__ int32_t hist_lds[4][IM_MAX_ACTIONS];
   __shared__ int32_t mw_lds[4][MW_NUM][IM_MAX_MODELS];
   __shared__ unsigned long long md_lds[4][MD_NUM][IM_MAX_MODELS];
-  __shared__ int64_t pend_k[4][kFront];   // refill candidate staging
-  __shared__ int32_t pend_i[4][kFront];
-  static_assert(sizeof(int4) * kStageChunks * 64 >= sizeof(int2) * 2 * refill_chunks<CHAIN>() * kFront,
-                "the refill buffer fits the stage");
+  __shared__ int32_t park[4][PK_NUM][IM_MAX_MODELS];
+  static_assert(sizeof(int4) * kStageChunks * 64 >= sizeof(int32_t) * kCandidates, "the candidate list fits the stage");
   static_assert(kStageChunks * 64 >= (C_NUM / 2) * IM_MAX_MODELS, "the counter staging fits the stage");
   static_assert(IM_MAX_MODELS < 63, "model 63 marks rows not admitted");
   const int lane = threadIdx.x & 63;
@@ -926,26 +931,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     uint64_t dry = ballot(npop_l > L.fn);
     if (dry != 0) {
       if (dry & wrote) wave_mem_sync();
+      // The per-model state waits in LDS meanwhile: the refill needs the
+      // registers for the pool's keys.
+      int32_t(*pk)[IM_MAX_MODELS] = park[wv];
+      if (lane < IM_MAX_MODELS) {
+        pk[PK_QLEN][lane] = L.qlen; pk[PK_BUSY][lane] = L.busy; pk[PK_EWMA][lane] = L.ewma;
+        pk[PK_BACKLOG][lane] = L.backlog; pk[PK_FH][lane] = L.fh; pk[PK_FN][lane] = L.fn;
+        pk[PK_P][lane] = L.P; pk[PK_MASK][lane] = L.busy_mask; pk[PK_DONE][lane] = L.next_done;
+        pk[PK_FMK][lane] = L.fmk; pk[PK_FMI][lane] = L.fmi; pk[PK_CHG][lane] = L.chg;
+      }
+      asm volatile("" ::: "memory");
       while (dry) {
         const int m = __builtin_ctzll(dry);
         dry &= dry - 1;
         const size_t em = em0 + m;
-        const int ofh = rl(L.fh, m), ofn = rl(L.fn, m);
-        int4 old = make_int4(0, 0, 0, 0);
-        int2 oldx = make_int2(0, 0);
-        if (lane < ofn) {
-          old = a.front[em * kFront + ofh + lane];
-          if constexpr (CHAIN) oldx = a.front_ext[em * kFront + ofh + lane];
-        }
+        const int ofh = __builtin_amdgcn_readfirstlane(pk[PK_FH][m]), ofn = __builtin_amdgcn_readfirstlane(pk[PK_FN][m]);
         Queue q;
-        q.P = rl(L.P, m);
+        q.P = __builtin_amdgcn_readfirstlane(pk[PK_P][m]);
         q.fh = 0;
         q.fn = 0;
         int4 fe;
         int2 fx;
         int4* pool = a.pool + em * a.qcap;
         int2* pool_x = CHAIN ? a.pool_ext + em * a.qcap : nullptr;
-        refill<CHAIN>(q, fe, fx, pool, pool_x, pend_k[wv], pend_i[wv], reinterpret_cast<int2*>(st), a.key_mode);
+        refill<CHAIN>(q, fe, fx, pool, pool_x, reinterpret_cast<int32_t*>(st), a.key_mode);
+        int4 old = make_int4(0, 0, 0, 0);
+        int2 oldx = make_int2(0, 0);
+        if (lane < ofn) {
+          old = a.front[em * kFront + ofh + lane];
+          if constexpr (CHAIN) oldx = a.front_ext[em * kFront + ofh + lane];
+        }
         const int nsel = q.fn;                                   // >= 1: P > 0
         const int nf = ofn + nsel < kFront ? ofn + nsel : kFront;
         const int back = ofn + nsel - nf;                        // largest selected entries returned
@@ -966,16 +981,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
           a.front[em * kFront + lane] = ne;
           if constexpr (CHAIN) a.front_ext[em * kFront + lane] = nx;
         }
-        const int32_t nk = rl(ne.x, nf - 1), ni = rl(ne.y, nf - 1);
-        if (lane == m) {
-          L.P = q.P;
-          L.fh = 0;
-          L.fn = nf;
-          L.fmk = nk;
-          L.fmi = ni;
-          L.chg |= CH_FRONT | CH_POOL;
+        if (lane == nf - 1) {
+          pk[PK_P][m] = q.P;
+          pk[PK_FH][m] = 0;
+          pk[PK_FN][m] = nf;
+          pk[PK_FMK][m] = ne.x;
+          pk[PK_FMI][m] = ne.y;
+          pk[PK_CHG][m] |= CH_FRONT | CH_POOL;
         }
         wrote |= 1ull << m;
+      }
+      asm volatile("" ::: "memory");
+      if (lane < IM_MAX_MODELS) {   // the other lanes hold no model
+        L.qlen = pk[PK_QLEN][lane]; L.busy = pk[PK_BUSY][lane]; L.ewma = pk[PK_EWMA][lane];
+        L.backlog = pk[PK_BACKLOG][lane]; L.fh = pk[PK_FH][lane]; L.fn = pk[PK_FN][lane];
+        L.P = pk[PK_P][lane]; L.busy_mask = pk[PK_MASK][lane]; L.next_done = pk[PK_DONE][lane];
+        L.fmk = pk[PK_FMK][lane]; L.fmi = pk[PK_FMI][lane]; L.chg = pk[PK_CHG][lane];
+      } else {
+        L = LaneState{};
       }
       wave_mem_sync();
     }
