@@ -520,38 +520,56 @@ __global__ __launch_bounds__(NW * 64, 1) void route_bf16_lds(RouteArgs a_in) {
   // Wave tile u is set up in two steps: its first loads (the CSR window and
   // the rows' q_idx and budget), then, once they have arrived, the env
   // lookup, the env's snapshot row and the embedding rows (row contexts and
-  // layer-1 B fragments).
+  // layer-1 B fragments). A 64-row tile has a row per lane: each lane looks its
+  // own row up and hands the two MFMA tiles what their gathers need.
+  constexpr int NC = NR == 2 ? 1 : NR;      // row contexts per lane
   struct First {
     EnvWindow w;
-    int32_t q[NR], bud[NR];
+    int32_t q[NC], bud[NC];
   };
   auto first_loads = [&](int32_t u) {
     First f;
     const int32_t r0 = u * WROWS;
     f.w = env_window(a, r0);
 #pragma unroll
-    for (int j = 0; j < NR; ++j) {
-      const int32_t r = r0 + 32 * j + n;
+    for (int j = 0; j < NC; ++j) {
+      const int32_t r = r0 + 32 * j + (NR == 2 ? lane : n);
       const int32_t rr = r < a.n_total ? r : a.n_total - 1;
       f.q[j] = a.q_idx[rr];
       f.bud[j] = a.budget[rr];
     }
     return f;
   };
-  auto setup = [&](int32_t u, const First& f, RowCtx (&c)[NR], u32x4 (&x)[NR][KB1], int gg) {
+  auto setup = [&](int32_t u, const First& f, RowCtx (&c)[NC], u32x4 (&x)[NR][KB1], int gg) {
     const int32_t r0 = u * WROWS;
     const int32_t rlast = (r0 + WROWS - 1 < a.n_total ? r0 + WROWS - 1 : a.n_total - 1);
-    int32_t rows[NR], envs[NR];
+    int32_t rows[NC], envs[NC];
 #pragma unroll
-    for (int j = 0; j < NR; ++j) rows[j] = r0 + 32 * j + n;
-    find_envs_in<NR>(a, f.w, r0, rlast, rows, envs);
+    for (int j = 0; j < NC; ++j) rows[j] = r0 + 32 * j + (NR == 2 ? lane : n);
+    find_envs_in<NC>(a, f.w, r0, rlast, rows, envs);
 #pragma unroll
-    for (int j = 0; j < NR; ++j) c[j] = row_ctx_from(a, rows[j], envs[j], f.q[j], f.bud[j]);
+    for (int j = 0; j < NC; ++j) c[j] = row_ctx_from(a, rows[j], envs[j], f.q[j], f.bud[j]);
     TailRaw<ED, KB1> raw[NR];
+    RowCtx t[NR];   // what the gathers read
+    if constexpr (NR == 2) {
+      int32_t tq[2], te[2], tb[2];
+      spread(c[0].q, tq);
+      spread(c[0].e, te);
+      spread(c[0].budget, tb);
 #pragma unroll
-    for (int j = 0; j < NR; ++j) gather_issue<ED, KB1>(a, c[j], gg, x[j], raw[j]);
+      for (int j = 0; j < 2; ++j) {
+        t[j].q = tq[j];
+        t[j].e = te[j];
+        t[j].budget = tb[j];
+      }
+    } else {
 #pragma unroll
-    for (int j = 0; j < NR; ++j) gather_finish<ED, KB1>(a, c[j], gg, x[j], raw[j]);
+      for (int j = 0; j < NR; ++j) t[j] = c[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) gather_issue<ED, KB1>(a, t[j], gg, x[j], raw[j]);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) gather_finish<ED, KB1>(a, t[j], gg, x[j], raw[j]);
   };
   // PIPE: the first wave tile is set up (first loads, then its gather)
   // while the block copies the weights into LDS, before the barrier, and each
@@ -559,7 +577,7 @@ __global__ __launch_bounds__(NW * 64, 1) void route_bf16_lds(RouteArgs a_in) {
   // layer 1 (its inputs are loop-carried: this pays only where the registers
   // are not all taken).
   int32_t u = ur.first + wave;
-  RowCtx c[NR];
+  RowCtx c[NC];
   u32x4 x[NR][KB1];
   First f0;
   if (PIPE && u < ur.end) f0 = first_loads(u);
@@ -692,8 +710,12 @@ __global__ __launch_bounds__(NW * 64, 1) void route_bf16_lds(RouteArgs a_in) {
       }
     }
     const int32_t un = u + NW;
+    if constexpr (NR == 2) {
+      epilogue64<AT, RL>(c[0], o, gg);
+    } else {
 #pragma unroll
-    for (int j = 0; j < NR; ++j) epilogue<AT, RL>(c[j], o[j], gg);
+      for (int j = 0; j < NR; ++j) epilogue<AT, RL>(c[j], o[j], gg);
+    }
     if (un >= ur.end) break;
     u = un;
     if constexpr (PIPE) setup(u, first_loads(u), c, x, gg);
@@ -1197,29 +1219,35 @@ struct LdsLaunch {
   int rows;    // 32-row MFMA tiles per wave
 };
 
-// 86 -> 256 -> 256 -> A, layer-1 weights through the caches: the greedy
-// route runs 8 waves (two per SIMD) of 64 rows, so every weight fragment read
-// from LDS or the caches feeds two MFMAs, with the next output tile's layer-1
-// fragments loaded while the current one is multiplied (up to 256 VGPRs per
-// wave); the RL outputs, whose epilogue needs more registers, and light
-// ticks, whose few tiles would leave most waves idle, run 16 waves of 32
-// rows; very light ticks 8 waves of 32 rows, software-pipelined.
+// 86 -> 256 -> 256 -> A, layer-1 weights through the caches: 8 waves (two per
+// SIMD) of 64 rows, so every weight fragment read from LDS or the caches feeds
+// two MFMAs and a row's setup and output run on a lane of its own, with the next
+// output tile's layer-1 fragments loaded while the current one is multiplied (up
+// to 256 VGPRs per wave). Light ticks, whose few tiles would leave most waves
+// idle, run 16 waves of 32 rows; very light greedy ones 8 waves of 32 rows,
+// software-pipelined. us, RL outputs, 32 / 64 rows per wave: 65,536 rows 17.6 /
+// 19.1, 262,144 rows 50.9 / 48.1, 2,097,152 rows 368 / 319.
 // 104 -> 256 -> A, every layer in LDS, software-pipelined, the output layer
-// consuming each hidden tile as soon as it is produced: the greedy route runs
-// 12 waves (three per SIMD, 168 VGPRs) of 64 rows, so each weight fragment
-// read from LDS feeds two MFMAs; the RL outputs run 16 waves of 32 rows (102
-// VGPRs). Returns a null kernel when no LDS-resident variant applies.
-LdsLaunch pick_lds(int dtype, int hidden, int n_layers, int out_tiles, int k1, int ed, bool rl, int light) {
+// consuming each hidden tile as soon as it is produced: 12 waves (three per SIMD,
+// 168 VGPRs) of 64 rows; the RL outputs below 1,024 rows per block run 16 waves
+// of 32 rows. us, RL outputs, 32 / 64 rows per wave: 131,072 rows 16.8 / 17.3,
+// 196,608 rows 21.4 / 22.5, 262,144 rows 27.7 / 26.2, 2,097,152 rows 180 / 172.
+// Returns a null kernel when no LDS-resident variant applies.
+LdsLaunch pick_lds(int dtype, int hidden, int n_layers, int out_tiles, int k1, int ed, bool rl, int light,
+                   int64_t rows_per_block) {
   if (dtype != IM_BF16) return {nullptr, 0, 0};
   if (hidden == 256 && n_layers == 3 && out_tiles == 1 && k1 == 6 && ed == 64) {
+    if (rl && light == 0) return {route_bf16_lds<256, 3, 1, 6, false, 8, 64, 2, 1, 6, false>, 8, 2};
     if (rl) return {route_bf16_lds<256, 3, 1, 6, false, 16, 64, 1, 1, 0, false>, 16, 1};
     if (light == 2) return {route_bf16_lds<256, 3, 1, 6, false, 8, 64, 1, 0, 6, true>, 8, 1};
     if (light == 1) return {route_bf16_lds<256, 3, 1, 6, false, 16, 64, 1, 0, 0, false>, 16, 1};
     return {route_bf16_lds<256, 3, 1, 6, false, 8, 64, 2, 0, 6, false>, 8, 2};
   }
-  if (hidden == 256 && n_layers == 2 && out_tiles == 1 && k1 == 7 && ed == 64)
-    return {rl ? route_bf16_lds<256, 2, 1, 7, true, 16, 64, 1, 1, 0, true>
-               : route_bf16_lds<256, 2, 1, 7, true, 12, 64, 2, 0, 0, true>, rl ? 16 : 12, rl ? 1 : 2};
+  if (hidden == 256 && n_layers == 2 && out_tiles == 1 && k1 == 7 && ed == 64) {
+    if (rl && rows_per_block < 1024) return {route_bf16_lds<256, 2, 1, 7, true, 16, 64, 1, 1, 0, true>, 16, 1};
+    return {rl ? route_bf16_lds<256, 2, 1, 7, true, 12, 64, 2, 1, 0, true>
+               : route_bf16_lds<256, 2, 1, 7, true, 12, 64, 2, 0, 0, true>, 12, 2};
+  }
   return {nullptr, 0, 0};
 }
 
@@ -1310,7 +1338,8 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
     // of 32 rows whose first tile's loads overlap the block's weight copy
     const int64_t rows = a.n_total, cap = (int64_t)64 * 8 * a.persistent_blocks;
     const int light = rows * 4 <= cap ? 2 : (rows * 4 <= 3 * cap ? 1 : 0);
-    const LdsLaunch kl = pick_lds(dtype, hidden, n_layers, out_tiles, a.k1, a.embed_dim, a.rl != 0, light);
+    const LdsLaunch kl = pick_lds(dtype, hidden, n_layers, out_tiles, a.k1, a.embed_dim, a.rl != 0, light,
+                                  rows / a.persistent_blocks);
     if (kl.k) {
       // one block per CU as long as there are wave tiles for them: a light
       // tick spreads its few tiles over every CU instead of filling a few

@@ -403,17 +403,22 @@ __device__ __forceinline__ void store_logits(KernArgs a, float* row, int act, fl
   }
 }
 
-// Masked argmax over the lane pair (n, n + 32), logits store, action store (or
-// the RL-rollout outputs). Lane (n, g) holds the actions 32 T + 8 (v / 4) + 4 g
-// + v % 4 of its row. RL: 0 = greedy route only, 1 = RL outputs only, 2 =
-// either, chosen by a->rl at run time.
-template <int AT, int RL = 2>
-__device__ __forceinline__ void epilogue(const RowCtx& c, const f32x16 (&acc)[AT], int g) {
-  const KernArgs a = late_args();
-  const bool rl = RL == 1 || (RL == 2 && a->rl);
+// One 32-row tile's part of the outputs: lane (n, g) holds the actions 32 T +
+// 8 (v / 4) + 4 g + v % 4 of its row n. `am` is the row's action mask, `id` and
+// `e` its request id and env (RL sampling). best: the row's largest valid logit
+// (both lanes of the pair); ba, r, val: this lane's part of the argmax, the sums
+// and the value row, to be joined with the other lane's.
+struct TileOut {
+  float best;
+  int32_t ba;
+  RlSums r;
+  float val;
+};
+template <int AT>
+__device__ __forceinline__ TileOut tile_out(KernArgs a, bool rl, uint64_t am, uint32_t id, int32_t e,
+                                            const f32x16 (&acc)[AT], int g) {
+  TileOut o;
   // bit 32 T + 8 j + i: action 32 T + 8 j + 4 g + i is masked
-  uint64_t am = c.amask;
-  asm volatile("" : "+v"(am));   // the shifted mask is formed here, not kept beside the mask since the row's setup
   const uint64_t inv = (uint64_t)((int64_t)~am >> (4 * g));
   const uint32_t mw[2] = {(uint32_t)inv, (uint32_t)(inv >> 32)};
   constexpr int AA = AT < 2 ? AT : 2;   // tiles with actions (at most 64; a third tile holds the value row only)
@@ -431,71 +436,160 @@ __device__ __forceinline__ void epilogue(const RowCtx& c, const f32x16 (&acc)[AT
     swap_halves<32>(as_int(best), x, y);
     best = max3(__int_as_float(x), __int_as_float(y), __int_as_float(y));
   }
-  int32_t ba = 127;
+  o.best = best;
+  o.ba = 127;
   if (!rl || a->greedy) {   // uniform
+    int32_t ba = 127;
 #pragma unroll
     for (int T = AA - 1; T >= 0; --T)
 #pragma unroll
       for (int v = 15; v >= 0; --v) ba = zm[T][v] == best ? 32 * T + 8 * (v >> 2) + (v & 3) : ba;
-    ba += 4 * g;
-    int32_t x, y;
-    swap_halves<32>(ba, x, y);
-    ba = x < y ? x : y;
-    // -1 when no action is valid; the first valid one when every valid logit is NaN
-    if (ba >= 64) ba = __ffsll((unsigned long long)c.amask) - 1;
+    o.ba = ba + 4 * g;
   }
-  if (rl) {
-    const bool sample = a->greedy == 0;
-    uint32_t id = 0;
-    if (sample) id = c.id >= 0 ? (uint32_t)c.id : request_id(a, c);
-    // the key schedule is formed per row group: hoisted out of the kernel's loop
-    // its 18 words would spill scalar registers into vector ones
-    uint32_t k0 = a->seed_lo, k1 = a->seed_hi;
-    asm volatile("" : "+s"(k0), "+s"(k1));
-    RlSums r;
-    float val = 0.f;
+  o.val = 0.f;
+  if (!rl) return o;
+  const bool sample = a->greedy == 0;
+  // the key schedule is formed per row group: hoisted out of the kernel's loop
+  // its 18 words would spill scalar registers into vector ones
+  uint32_t k0 = a->seed_lo, k1 = a->seed_hi;
+  asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
-    for (int T = 0; T < AT; ++T) {
+  for (int T = 0; T < AT; ++T) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int a0 = 32 * T + 8 * j;   // the lane pair's 8 actions: two Philox blocks
-        const float z[4] = {acc[T][4 * j], acc[T][4 * j + 1], acc[T][4 * j + 2], acc[T][4 * j + 3]};
-        if (T < AA && a0 < a->A) {        // uniform
-          const uint32_t mb = mw[T < AA ? T : 0] >> (8 * j);
-          if (sample) {
-            const uint4 w = philox10(make_uint4(id, (uint32_t)c.e, (uint32_t)((a0 >> 2) + g), 0u), k0, k1);
-            rl_block<true>(r, z, mb, best, a0 + 4 * g, w);
-          } else {
-            rl_block<false>(r, z, mb, best, a0 + 4 * g, make_uint4(0, 0, 0, 0));
-          }
-        }
-        if (a->value && (a->A >> 3) == 4 * T + j) {   // uniform: the group of row A
-          const int i = a->A & 3;
-          const float v = i == 0 ? z[0] : (i == 1 ? z[1] : (i == 2 ? z[2] : z[3]));
-          val = ((a->A >> 2) & 1) == g ? v : 0.f;
+    for (int j = 0; j < 4; ++j) {
+      const int a0 = 32 * T + 8 * j;   // the lane pair's 8 actions: two Philox blocks
+      const float z[4] = {acc[T][4 * j], acc[T][4 * j + 1], acc[T][4 * j + 2], acc[T][4 * j + 3]};
+      if (T < AA && a0 < a->A) {        // uniform
+        const uint32_t mb = mw[T < AA ? T : 0] >> (8 * j);
+        if (sample) {
+          const uint4 w = philox10(make_uint4(id, (uint32_t)e, (uint32_t)((a0 >> 2) + g), 0u), k0, k1);
+          rl_block<true>(o.r, z, mb, best, a0 + 4 * g, w);
+        } else {
+          rl_block<false>(o.r, z, mb, best, a0 + 4 * g, make_uint4(0, 0, 0, 0));
         }
       }
+      if (a->value && (a->A >> 3) == 4 * T + j) {   // uniform: the group of row A
+        const int i = a->A & 3;
+        const float v = i == 0 ? z[0] : (i == 1 ? z[1] : (i == 2 ? z[2] : z[3]));
+        o.val = ((a->A >> 2) & 1) == g ? v : 0.f;
+      }
     }
+  }
+  return o;
+}
+
+// A tile's logits, 32 rows from row r0 on (the row's other lane stores the rest).
+template <int AT>
+__device__ __forceinline__ void store_tile_logits(KernArgs a, int32_t r, int32_t bad, const f32x16 (&acc)[AT], int g) {
+  float* out = a->logits + (size_t)r * a->A;
+#pragma unroll
+  for (int T = 0; T < AT; ++T) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float z0 = bad ? 0.f : acc[T][4 * j], z1 = bad ? 0.f : acc[T][4 * j + 1];
+      const float z2 = bad ? 0.f : acc[T][4 * j + 2], z3 = bad ? 0.f : acc[T][4 * j + 3];
+      store_logits(a, out, 32 * T + 8 * j + 4 * g, z0, z1, z2, z3);
+    }
+  }
+}
+
+// The action of a row from its joined argmax: -1 when no action is valid, the
+// first valid one when every valid logit is NaN.
+__device__ __forceinline__ int32_t argmax_of(int32_t ba, uint64_t am) {
+  return ba >= 64 ? __ffsll((unsigned long long)am) - 1 : ba;
+}
+
+// Masked argmax over the lane pair (n, n + 32), logits store, action store (or
+// the RL-rollout outputs). RL: 0 = greedy route only, 1 = RL outputs only, 2 =
+// either, chosen by a.rl at run time.
+template <int AT, int RL = 2>
+__device__ __forceinline__ void epilogue(const RowCtx& c, const f32x16 (&acc)[AT], int g) {
+  const KernArgs a = late_args();
+  const bool rl = RL == 1 || (RL == 2 && a->rl);
+  uint64_t am = c.amask;
+  asm volatile("" : "+v"(am));   // the shifted mask is formed here, not kept beside the mask since the row's setup
+  uint32_t id = 0;
+  if (rl && a->greedy == 0) id = c.id >= 0 ? (uint32_t)c.id : request_id(a, c);
+  TileOut o = tile_out<AT>(a, rl, am, id, c.e, acc, g);
+  int32_t x, y;
+  swap_halves<32>(o.ba, x, y);
+  const int32_t ba = argmax_of(x < y ? x : y, c.amask);
+  if (rl) {
     auto other = [](float v) { return __int_as_float(xshfl<32>(as_int(v))); };
-    rl_join(r, other(r.s), other(r.sz), other(r.bs), other(r.bz), xshfl<32>(r.ba));
-    val += other(val);   // one lane of the pair holds row A
-    if (c.live && g == 0) rl_store(a, c, r, best, ba, val);
+    rl_join(o.r, other(o.r.s), other(o.r.sz), other(o.r.bs), other(o.r.bz), xshfl<32>(o.r.ba));
+    o.val += other(o.val);   // one lane of the pair holds row A
+    if (c.live && g == 0) rl_store(a, c, o.r, o.best, ba, o.val);
   } else if (c.live && g == 0) {
     a->actions[c.r] = c.bad ? -1 : ba;
     if (c.bad) atomicOr(a->err, c.bad);
   }
-  if (!c.live) return;
+  if (c.live && a->logits) store_tile_logits<AT>(a, c.r, c.bad, acc, g);
+}
+
+// Two registers v0, v1 that hold tile 0's and tile 1's value in every lane pair:
+// x gets the lower lane's and y the upper lane's value of the row this lane owns
+// (lane l: row l of the 64, the lower half of the lanes tile 0's rows).
+__device__ __forceinline__ void own_halves(int32_t v0, int32_t v1, int32_t& x, int32_t& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(v0, v1, false, false);
+  x = (int32_t)r[0];
+  y = (int32_t)r[1];
+}
+// This lane's value of the row it owns, handed to both lanes of the tiles' pairs:
+// t[0] for tile 0's row, t[1] for tile 1's.
+__device__ __forceinline__ void spread(int32_t v, int32_t (&t)[2]) { swap_halves<32>(v, t[0], t[1]); }
+
+// The same outputs for a wave tile of 64 rows (two 32-row MFMA tiles) whose row
+// contexts lie one per lane: c is lane l's row r0 + l. The parts of a row meet in
+// the lane that owns it, so what follows the matrix work per row (softmax
+// normalisation, stores) runs once per 64 rows on full lanes.
+template <int AT, int RL>
+__device__ __forceinline__ void epilogue64(const RowCtx& c, const f32x16 (&acc)[2][AT], int g) {
+  static_assert(RL == 0 || RL == 1, "greedy or RL outputs");
+  const KernArgs a = late_args();
+  uint64_t am = c.amask;
+  asm volatile("" : "+v"(am));
+  int32_t lo[2], hi[2], id[2] = {0, 0}, e[2] = {0, 0};
+  spread((int32_t)(uint32_t)am, lo);
+  spread((int32_t)(am >> 32), hi);
+  if (RL && a->greedy == 0) {
+    spread((int32_t)request_id(a, c), id);
+    spread(c.e, e);
+  }
+  TileOut o[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    o[j] = tile_out<AT>(a, RL == 1, (uint64_t)(uint32_t)hi[j] << 32 | (uint32_t)lo[j], (uint32_t)id[j], e[j], acc[j], g);
+  int32_t x, y;
+  own_halves(o[0].ba, o[1].ba, x, y);
+  const int32_t ba = argmax_of(x < y ? x : y, am);
+  if constexpr (RL == 1) {
+    RlSums r;
+    auto meet = [](float v0, float v1, float& p, float& q) {
+      int32_t s, t;
+      own_halves(as_int(v0), as_int(v1), s, t);
+      p = __int_as_float(s);
+      q = __int_as_float(t);
+    };
+    float s, sz, bs, bz, v0, v1;
+    meet(o[0].r.s, o[1].r.s, r.s, s);
+    meet(o[0].r.sz, o[1].r.sz, r.sz, sz);
+    meet(o[0].r.bs, o[1].r.bs, r.bs, bs);
+    meet(o[0].r.bz, o[1].r.bz, r.bz, bz);
+    own_halves(o[0].r.ba, o[1].r.ba, r.ba, x);
+    rl_join(r, s, sz, bs, bz, x);
+    meet(o[0].val, o[1].val, v0, v1);   // one lane of the pair holds row A
+    if (c.live) rl_store(a, c, r, g ? o[1].best : o[0].best, ba, v0 + v1);
+  } else if (c.live) {
+    a->actions[c.r] = c.bad ? -1 : ba;
+    if (c.bad) atomicOr(a->err, c.bad);
+  }
   if (a->logits) {
-    float* out = a->logits + (size_t)c.r * a->A;
+    int32_t bad[2], r[2];
+    spread(c.bad, bad);
+    spread(c.live ? c.r : -1, r);
 #pragma unroll
-    for (int T = 0; T < AT; ++T) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float z0 = c.bad ? 0.f : acc[T][4 * j], z1 = c.bad ? 0.f : acc[T][4 * j + 1];
-        const float z2 = c.bad ? 0.f : acc[T][4 * j + 2], z3 = c.bad ? 0.f : acc[T][4 * j + 3];
-        store_logits(a, out, 32 * T + 8 * j + 4 * g, z0, z1, z2, z3);
-      }
-    }
+    for (int j = 0; j < 2; ++j)
+      if (r[j] >= 0) store_tile_logits<AT>(a, r[j], bad[j], acc[j], g);
   }
 }
 
