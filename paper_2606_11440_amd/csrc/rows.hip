@@ -15,16 +15,18 @@ constexpr int kScanThreads = 1024;
 
 // Arrivals of env e the route step takes: a CSR entry outside the arrays
 // contributes none (the schedule step reports it and skips the env).
-__device__ __forceinline__ int32_t usable_arrivals(const RowsArgs& a, int e) {
-  const int32_t lo = a.offsets[e], hi = a.offsets[e + 1];
+__device__ __forceinline__ int32_t usable(const RowsArgs& a, int32_t lo, int32_t hi) {
   return (lo < 0 || hi < lo || hi > a.n_total || hi - lo > a.max_arrivals) ? 0 : hi - lo;
 }
 
 // One block: exclusive scan of (pending + usable arrivals) over the envs.
 // Each thread holds the counts of kPer consecutive envs in registers; wave
 // scans by shuffles, the 16 wave totals scanned by the first wave; blocks of
-// 1024 * kPer envs in sequence with a carried total.
-constexpr int kPer = 8;
+// 1024 * kPer envs in sequence with a carried total. Latency-bound: the tick,
+// the offsets and the pending counts of both parities (the tick picks one) are
+// in flight together, and the CSR is checked on the offsets already loaded.
+// 4,096 envs: 8.1 -> 6.4 us (three dependent round trips before).
+constexpr int kPer = 4;
 
 __device__ __forceinline__ int32_t wave_incl_scan(int32_t x, int lane) {
 #pragma unroll
@@ -39,23 +41,39 @@ __global__ __launch_bounds__(kScanThreads) void rows_scan_kernel(RowsArgs a) {
   constexpr int NWAVE = kScanThreads / 64;
   __shared__ int32_t wsum[NWAVE];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // envs tid kPer + j of the block of envs at base: their offsets and the
+  // pending counts of either parity
+  int32_t off[kPer + 1], pc0[kPer], pc1[kPer];
+  auto load = [&](int base) {
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int e = min(base + tid * kPer + j, a.E - 1);
+      off[j] = a.offsets[min(base + tid * kPer + j, a.E)];
+      pc0[j] = a.pcnt[e];
+      pc1[j] = a.pcnt[(size_t)a.E + e];
+    }
+    off[kPer] = a.offsets[min(base + tid * kPer + kPer, a.E)];
+  };
+  load(0);
   const int32_t t = a.ms[0].t;
-  const int32_t* pc = a.pcnt + (size_t)(t & 1) * a.E;
+  const int32_t first = a.offsets[0], total = a.offsets[a.E];
   // The rows are laid out by a scan over the arrival CSR, so it must be one
   // monotone partition of [0, n_total); otherwise no arrival is usable (every
   // env then skips the tick in the schedule step).
-  int broken = 0;
-  if (tid == 0) broken = a.offsets[0] != 0 || a.offsets[a.E] != a.n_total;
-  for (int e = tid; e < a.E; e += kScanThreads) broken |= a.offsets[e + 1] < a.offsets[e];
+  int broken = first != 0 || total != a.n_total;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) broken |= tid * kPer + j < a.E && off[j + 1] < off[j];
+  for (int e = kScanThreads * kPer + tid; e < a.E; e += kScanThreads) broken |= a.offsets[e + 1] < a.offsets[e];
   const bool whole = __syncthreads_or(broken) == 0;
   int32_t carry = 0;
   for (int base = 0; base < a.E; base += kScanThreads * kPer) {
+    if (base != 0) load(base);
     int32_t c[kPer];
     int32_t sum = 0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       const int e = base + tid * kPer + j;
-      c[j] = e < a.E ? pc[e] + (whole ? usable_arrivals(a, e) : 0) : 0;
+      c[j] = e < a.E ? ((t & 1) ? pc1[j] : pc0[j]) + (whole ? usable(a, off[j], off[j + 1]) : 0) : 0;
       sum += c[j];
     }
     const int32_t x = wave_incl_scan(sum, lane);
@@ -90,17 +108,18 @@ __global__ __launch_bounds__(256) void rows_gather_kernel(RowsArgs a) {
   const int e = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (e >= a.E) return;
   const int32_t t = a.ms[0].t;
-  const int32_t pc = a.pcnt[(size_t)(t & 1) * a.E + e];
-  const int4* pend = a.pend + ((size_t)(t & 1) * a.E + e) * a.pend_cap;
+  const int32_t pc0 = a.pcnt[e], pc1 = a.pcnt[(size_t)a.E + e];   // both parities, not waiting for the tick
+  const int32_t lo = a.offsets[e], hi = a.offsets[e + 1], whole = a.n_rows[1] == 0;   // n_rows: the scan kernel's
   const int32_t base = a.roff[e];
+  const int32_t pc = (t & 1) ? pc1 : pc0;
+  const int4* pend = a.pend + ((size_t)(t & 1) * a.E + e) * a.pend_cap;
+  const int32_t na = whole ? usable(a, lo, hi) : 0;
   for (int i = lane; i < pc; i += 64) {
     const int4 p = pend[i];
     a.rq[base + i] = chain_q(p.x);
     a.rb[base + i] = (int16_t)remaining_budget(p.z, t);
     a.rr[base + i] = (int16_t)(a.n_roles > 0 ? (chain_role0(p.y) + chain_k(p.x)) % a.n_roles : 0);
   }
-  const int32_t na = a.n_rows[1] == 0 ? usable_arrivals(a, e) : 0;   // written by the scan kernel
-  const int32_t lo = a.offsets[e];
   for (int i = lane; i < na; i += 64) {
     a.rq[base + pc + i] = a.q_idx[lo + i];
     a.rb[base + pc + i] = a.budget[lo + i];
