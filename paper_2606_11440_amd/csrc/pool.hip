@@ -171,7 +171,7 @@ __global__ void set_rpm_kernel(ModelRec* r, int32_t limit, float inv) {
 // network over the next power of two; every pool key exceeds every front key).
 // A pool of more than kExportSort entries goes out unsorted and is sorted on the
 // host. Reading 16 envs x 5 models x 256 entries: seven copies and 80 host sorts
-// took 500 us, this takes 60 (bound by the two synchronisations and the stores
+// took 500 us, this takes 42 (bound by the two synchronisations and the stores
 // over PCIe).
 constexpr int kExportSort = 4096;                  // 64 KB of LDS
 constexpr size_t kExportBytes = size_t(4) << 20;   // pinned staging: a larger range goes in several launches

@@ -2,16 +2,18 @@
 //
 // Sec. 3 Eq. 1 (the executor's state), Sec. 3 "Action" (a -> model a / K,
 // depth a % K) and Sec. 4.2 (a policy network scores every joint action; it
-// is deployed greedily here). One wave owns 32 request rows; a block holds 4
-// waves (128 rows).
+// is deployed greedily here). A wave owns 32 or 64 request rows of the persistent
+// kernels; in the feature-split kernels a block owns the rows and each wave some
+// of every hidden layer's features.
 //
 // The MLP is evaluated transposed, Y^T = W X^T, on 32x32 MFMA tiles: the
-// weights are the A operand (streamed from L2, pre-packed so that each lane
+// weights are the A operand (from LDS or L2, pre-packed so that each lane
 // reads 16 contiguous bytes per instruction) and the activations are the B
 // operand. The accumulator layout of one layer (lane = row n + 32 g, register v
 // holds output feature 8(v/4) + 4g + v%4 of its tile) is used directly as the
 // B operand of the next layer; the next layer's weight columns are permuted at
-// pool creation to match, so activations never leave registers.
+// pool creation to match, so a wave's activations never leave registers (the
+// feature-split kernels hand them to the other waves through LDS).
 //
 // bf16 pools use v_mfma_f32_32x32x16_bf16 (fp32 accumulate, hidden activations
 // rounded to bf16 after the ReLU); fp32 pools use v_mfma_f32_16x16x4_f32 on

@@ -21,7 +21,8 @@
 //                 pool. The front array is written once per tick, if changed.
 //   service    -- free slots below c_m are filled in slot order from the front
 //                 head; when the front runs empty it is refilled with the 64
-//                 smallest pool entries (bitonic top-64 selection), and the
+//                 smallest pool entries (sampled threshold, then a sort of the
+//                 few keys below it), and the
 //                 pool is compacted. Busy slots then advance one tick; a
 //                 request completes when its remaining time reaches 0 (latency
 //                 EWMA with alpha = 1/8 in Q8, Sec. 5.4; bounded concurrency
@@ -1208,7 +1209,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
 // correctly rounded fp64 steps (no completion leaves lambda unchanged).
 // Latency-bound: one round trip over 16 KB. Summing the per-model counters here
 // instead (a grid of up to 1,024 blocks, three contended atomics each) took 6 us
-// at 20,480 (env, model) rows and 47 us at 524,288; this takes 3 us at any size.
+// at 20,480 (env, model) rows and 47 us at 524,288; this takes 3 to 4.5 us at any
+// size.
 __global__ __launch_bounds__(256) void dual_update_kernel(const int64_t* shards, int64_t* last, double eta,
                                                           double lambda_max, double* lambda) {
   __shared__ int64_t part[2][4];
