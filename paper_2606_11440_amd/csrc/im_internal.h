@@ -124,6 +124,7 @@ struct RouteArgs {
   int32_t* err;
   int32_t persistent_blocks;          // grid of the persistent kernels (0: never use them)
   int32_t cus;                        // compute units of the device
+  int32_t pair_blocks;                // fp32 feature-split kernel: blocks of two row tiles, before those of one
   // RL-rollout outputs (im_route_sample)
   int32_t rl;                         // 1: log-prob, entropy, value; sampled or greedy action
   int32_t greedy;                     // with rl: 1 = masked argmax, 0 = Gumbel-max sample

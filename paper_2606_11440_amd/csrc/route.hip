@@ -348,21 +348,18 @@ __device__ __forceinline__ void layer16_out(const f32x4* W, int KG, const f32x4*
 // activations through LDS (one buffer, rewritten layer by layer), and wave j
 // computes the output layer and the epilogue of row tile j. The features come
 // in once per block, a group (four K steps) per wave in turn.
+template <int H>
+constexpr int kF32Groups = H / 16 < 8 ? 8 : H / 16;   // groups of features in LDS at a time
 template <int H, int NL, int AT, int NR>
-__global__ __launch_bounds__(256) void route_f32s(RouteArgs a_in) {
-  // chain pools: the tick's row count is on the device
-  RouteArgs a = a_in;
-  if (a_in.n_total_dev) a.n_total = min(*a_in.n_total_dev, a_in.n_total);   // the caller's buffers bound it
+__device__ __forceinline__ void f32s_block(const RouteArgs& a, int32_t row0, f32x4* hs) {
   constexpr int TH = H / 16, TQ = TH / 4, KGH = H / 16, ROWS = 16 * NR;
-  constexpr int KC = KGH < 8 ? 8 : KGH;      // groups of features in LDS at a time
+  constexpr int KC = kF32Groups<H>;
   constexpr int NP = TQ >= 4 ? 1 : 4;        // partial sums of the hidden layers after the first
   constexpr int NPO = AT >= 4 ? 1 : 4;       // of the output layer
   static_assert(TH % 4 == 0, "hidden tiles split four ways");
-  __shared__ f32x4 hs[KC * NR * 64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, q = lane >> 4;
-  const int32_t row0 = (int32_t)blockIdx.x * ROWS;
   if (row0 >= a.n_total) return;   // the whole block (chain pools' bound launch)
   const int T0 = wave * TQ;
   const int KG1 = (a.k1 + 3) / 4;
@@ -449,6 +446,22 @@ __global__ __launch_bounds__(256) void route_f32s(RouteArgs a_in) {
       if constexpr (NPO == 4) out[T] = (out[T] + acc[T][0][1]) + (acc[T][0][2] + acc[T][0][3]);
     }
     epilogue16<AT>(c[j], out, q);
+  }
+}
+// NR 2: the first a.pair_blocks blocks take 32 rows, the others 16.
+template <int H, int NL, int AT, int NR>
+__global__ __launch_bounds__(256) void route_f32s(RouteArgs a_in) {
+  // chain pools: the tick's row count is on the device
+  RouteArgs a = a_in;
+  if (a_in.n_total_dev) a.n_total = min(*a_in.n_total_dev, a_in.n_total);   // the caller's buffers bound it
+  __shared__ f32x4 hs[kF32Groups<H> * NR * 64];
+  const int32_t b = (int32_t)blockIdx.x;
+  if constexpr (NR == 1) {
+    f32s_block<H, NL, AT, 1>(a, 16 * b, hs);
+  } else if (b < a.pair_blocks) {   // uniform
+    f32s_block<H, NL, AT, 2>(a, 32 * b, hs);
+  } else {
+    f32s_block<H, NL, AT, 1>(a, 16 * (a.pair_blocks + b), hs);
   }
 }
 
@@ -1370,10 +1383,27 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
   // 449 -> 256 -> 64 at 4,096 rows 22.6 / 30.8, 16,384 rows 58.0 / 49.4.
   const int nr = a.n_total <= 16 * a.cus ? 1 : 2;
   RouteKernel k = n_layers == 2 ? pick<2>(hidden, out_tiles, nr) : pick<3>(hidden, out_tiles, nr);
-  // blocks of 4 waves: 16 rows per wave (hidden width 32) or 16 nr rows per block (feature-split)
-  const int rows = hidden % 64 == 0 ? 16 * nr : 64;
-  const unsigned blocks = (unsigned)((a.n_total + rows - 1) / rows);
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, a);
+  // With two, the rows past the last whole round of 32-row blocks (one per
+  // compute unit) go in 16-row blocks if these fit one per compute unit: a few
+  // rows more than whole rounds then cost their units half a block. us per
+  // launch with 32-row blocks only / with the tail in 16-row blocks, 86 -> 256 ->
+  // 256 -> 15: 8,250 rows 30.9 / 26.2, 16,400 rows 43.0 / 37.5, 20,480 rows 45.6 /
+  // 40.4, 33,000 rows 74.7 / 66.1; 54 -> 64 -> 15: 16,400 rows 7.2 / 6.7. Past half
+  // a round the tail would need two 16-row blocks on some units, which a 32-row
+  // block does in less time.
+  RouteArgs f = a;
+  unsigned blocks;
+  if (hidden % 64 != 0) {
+    blocks = (unsigned)((a.n_total + 63) / 64);   // 4 waves of 16 rows
+  } else if (nr == 1) {
+    blocks = (unsigned)((a.n_total + 15) / 16);
+  } else {
+    const int round = 32 * a.cus, rest = a.n_total % round;
+    const bool tail = rest <= 16 * a.cus;
+    f.pair_blocks = tail ? (a.n_total - rest) / 32 : (a.n_total + 31) / 32;
+    blocks = (unsigned)(f.pair_blocks + (tail ? (rest + 15) / 16 : 0));
+  }
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, f);
   return hipGetLastError();
 }
 
