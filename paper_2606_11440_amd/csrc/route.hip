@@ -1344,8 +1344,10 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
   //   86 -> 256 -> 256 -> 15   9.6 / 8.0, 10.0 / 9.4, 10.9 / 12.4, 17.0 / 18.7
   //   104 -> 256 -> 24         8.7 / 6.2, 9.0 / 7.4, 9.6 / 9.2, 11.2 / 12.6
   //   193 -> 512 -> 512 -> 64  37.9 / 18.0, 38.3 / 22.3, 40.5 / 31.5, 49.1 / 59.8
+  const bool persistent = pick_lds(dtype, hidden, n_layers, out_tiles, a.k1, a.embed_dim, false, 0, 0).k ||
+                          pick_stream(dtype, hidden, n_layers, out_tiles, a.k1, a.embed_dim, false);   // the shape has such a kernel
   const int64_t split_rows = (int64_t)(hidden == 512 ? 128 : 64) * a.persistent_blocks;
-  if (dtype == IM_BF16 && a.n_total <= split_rows) return launch_split(a, hidden, n_layers, out_tiles, s);
+  if (dtype == IM_BF16 && a.n_total <= split_rows) return launch_split(a, hidden, n_layers, out_tiles, !persistent, s);
   if (a.persistent_blocks > 0) {
     // a light tick (at most three 64-row tiles per four waves of 8-wave
     // blocks) runs the 16-wave, 32-row shape: twice the waves share its rows;
@@ -1375,7 +1377,7 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
       return hipGetLastError();
     }
   }
-  if (dtype == IM_BF16) return launch_split(a, hidden, n_layers, out_tiles, s);
+  if (dtype == IM_BF16) return launch_split(a, hidden, n_layers, out_tiles, !persistent, s);
   // One 16-row tile per block while the blocks fit one per compute unit (a
   // block's latency bounds the launch), else two, which halves the weight bytes
   // from L2 per MFMA. us per launch at 1 / 2 tiles: 86 -> 256 -> 256 -> 15 at

@@ -10,8 +10,12 @@
 // replaces its input in LDS (the accumulators hold it across the barrier). The
 // output layer and the epilogue take one 32-row tile per wave.
 //
-// Sums run in the order of the persistent kernels (bias first, K ascending),
-// so the logits are the same bit for bit.
+// K ascends in every sum. With BL the bias is added to the finished sum; without,
+// the sum starts from it, as in the persistent kernels, so that a shape that has
+// one gets the same logits from both bit for bit. The two differ where an
+// activation rounds to bf16 the other way (logits 1e-5 to 1e-4 apart, now and then
+// an action), so a shape keeps the order it has: BL where it has no persistent
+// kernel.
 #pragma once
 #include "route_dev.h"
 
@@ -68,7 +72,7 @@ struct WeightRing {
   }
 };
 
-template <int H, int NL, int AT, int NR, int TPW>
+template <int H, int NL, int AT, int NR, int TPW, bool BL>
 __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 3 : 4) : (NR == 2 ? 3 : 2)) void route_bf16_split(RouteArgs a_in) {
   // chain pools: the tick's row count is on the device
   RouteArgs a = a_in;
@@ -91,9 +95,18 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
   const int T0 = wave * TPW;
   const u32x4* W1 = (const u32x4*)a.W[0] + (size_t)T0 * a.k1 * 64 + lane;
   ring.start(W1, a.k1 * 64, a.k1 < KC ? a.k1 : KC);
-  f32x16 acc[TPW][NR];
+  f32x16 acc[TPW][NR], bias[TPW];
+  auto load_bias = [&](const float* b) {
 #pragma unroll
-  for (int t = 0; t < TPW; ++t) acc[t][0] = *(const f32x16*)(a.bias[0] + ((T0 + t) * 2 + g) * 16);
+    for (int t = 0; t < TPW; ++t) bias[t] = *(const f32x16*)(b + ((T0 + t) * 2 + g) * 16);
+  };
+  auto start_sums = [&]() {
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int j = 0; j < NR; ++j) acc[t][j] = BL ? f32x16{} : bias[t];
+  };
+  load_bias(a.bias[0]);
 
   const bool aligned = (a.embed_dim & 7) == 0 && ((uintptr_t)a.emb & 15) == 0;   // 16-byte aligned rows
   const int ke = aligned ? a.embed_dim / 16 : 0;   // K blocks that are all embedding
@@ -160,10 +173,7 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
   lds_barrier();
 
   // ---- layer 1 ----
-#pragma unroll
-  for (int t = 0; t < TPW; ++t)
-#pragma unroll
-    for (int j = 1; j < NR; ++j) acc[t][j] = acc[t][0];
+  start_sums();
   for (int k0 = 0; k0 < a.k1; k0 += KC) {
     const int kn = a.k1 - k0 < KC ? a.k1 - k0 : KC;
     if (k0 != 0) {
@@ -183,7 +193,7 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
 #pragma unroll
       for (int j = 0; j < NR; ++j) {
         u32x4 f0, f1;
-        relu_to_frags(acc[t][j], f0, f1);
+        relu_to_frags(BL ? acc[t][j] + bias[t] : acc[t][j], f0, f1);
         buf[((2 * (T0 + t)) * NR + j) * 64 + lane] = f0;
         buf[((2 * (T0 + t) + 1) * NR + j) * 64 + lane] = f1;
       }
@@ -194,12 +204,8 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
     ring.start((const u32x4*)a.W[1] + (size_t)T0 * KH * 64 + lane, KH * 64, KH);
     lds_barrier();   // every wave is done reading the features
     store_frags();
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      acc[t][0] = *(const f32x16*)(a.bias[1] + ((T0 + t) * 2 + g) * 16);
-#pragma unroll
-      for (int j = 1; j < NR; ++j) acc[t][j] = acc[t][0];
-    }
+    load_bias(a.bias[1]);
+    start_sums();
     lds_barrier();
     ring.run(buf + lane, acc);
   }
@@ -212,9 +218,12 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
   lds_barrier();
 #pragma unroll 1
   for (int j = wave; j < NR; j += NW) {
-    f32x16 out[AT][1];
+    f32x16 out[AT], ob[AT];
 #pragma unroll
-    for (int T = 0; T < AT; ++T) out[T][0] = *(const f32x16*)(a.bias[NL - 1] + (T * 2 + g) * 16);
+    for (int T = 0; T < AT; ++T) {
+      ob[T] = *(const f32x16*)(a.bias[NL - 1] + (T * 2 + g) * 16);
+      out[T] = BL ? f32x16{} : ob[T];
+    }
     if (j != wave) last.start((const u32x4*)a.W[NL - 1] + lane, KH * 64, KH);
     // this row tile's fragments are NR apart
     const u32x4* b = buf + j * 64 + lane;
@@ -226,7 +235,7 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
         if (kb < KH) {
           const u32x4 x = b[kb * NR * 64];
 #pragma unroll
-          for (int T = 0; T < AT; ++T) out[T][0] = mfma_bf16(last.r[d][T], x, out[T][0]);
+          for (int T = 0; T < AT; ++T) out[T] = mfma_bf16(last.r[d][T], x, out[T]);
           if (kb + 4 < KH) {
 #pragma unroll
             for (int T = 0; T < AT; ++T) last.r[d][T] = last.at(kb + 4, T);
@@ -244,10 +253,11 @@ __global__ __launch_bounds__(H / 32 / TPW * 64, NR == 1 ? (AT == 3 && H < 512 ? 
     r.bad = s_bad[i];
     r.id = s_id[i];
     r.amask = s_m[i];
-    f32x16 o[AT];
+    if constexpr (BL) {
 #pragma unroll
-    for (int T = 0; T < AT; ++T) o[T] = out[T][0];
-    epilogue<AT>(r, o, g);
+      for (int T = 0; T < AT; ++T) out[T] += ob[T];
+    }
+    epilogue<AT>(r, out, g);
   }
 }
 
@@ -257,23 +267,31 @@ struct SplitLaunch {
   int waves, rows;
 };
 
+template <int H, int NL, int AT, int NR, int TPW>
+RouteKernel split_kernel(bool bias_last) {
+  // the shapes (in part) that the persistent kernels cover
+  if constexpr ((H == 256 && AT == 1) || (H == 512 && NL == 3 && AT >= 2)) {
+    if (!bias_last) return route_bf16_split<H, NL, AT, NR, TPW, false>;
+  }
+  return route_bf16_split<H, NL, AT, NR, TPW, true>;
+}
 template <int H, int NL, int NR, int TPW>
-SplitLaunch pick_at(int at) {
-  RouteKernel k = at == 1 ? route_bf16_split<H, NL, 1, NR, TPW>
-                          : (at == 2 ? route_bf16_split<H, NL, 2, NR, TPW> : route_bf16_split<H, NL, 3, NR, TPW>);
+SplitLaunch pick_at(int at, bool bias_last) {
+  RouteKernel k = at == 1 ? split_kernel<H, NL, 1, NR, TPW>(bias_last)
+                          : (at == 2 ? split_kernel<H, NL, 2, NR, TPW>(bias_last) : split_kernel<H, NL, 3, NR, TPW>(bias_last));
   return {k, H / 32 / TPW, 32 * NR};
 }
 template <int H, int NL>
-SplitLaunch pick_rows(int at, int size) {
-  if (size == 0 || H == 32) return pick_at<H, NL, 1, 1>(at);   // hidden 32: one wave a block
+SplitLaunch pick_rows(int at, bool bias_last, int size) {
+  if (size == 0 || H == 32) return pick_at<H, NL, 1, 1>(at, bias_last);   // hidden 32: one wave a block
   if constexpr (H >= 256) {
-    if (size == 2) return pick_at<H, NL, 4, 2>(at);
+    if (size == 2) return pick_at<H, NL, 4, 2>(at, bias_last);
   }
-  if constexpr (H > 32) return pick_at<H, NL, 2, H == 512 ? 2 : 1>(at);
+  if constexpr (H > 32) return pick_at<H, NL, 2, H == 512 ? 2 : 1>(at, bias_last);
 }
 template <int H>
-SplitLaunch pick_nl(int nl, int at, int size) {
-  return nl == 2 ? pick_rows<H, 2>(at, size) : pick_rows<H, 3>(at, size);
+SplitLaunch pick_nl(int nl, int at, bool bias_last, int size) {
+  return nl == 2 ? pick_rows<H, 2>(at, bias_last, size) : pick_rows<H, 3>(at, bias_last, size);
 }
 
 bool split_supported(int hidden) {
@@ -292,16 +310,17 @@ bool split_supported(int hidden) {
 //                            131,072 rows 111 / 78 / 64
 //   97 -> 128 -> 128 -> 32   8,192 rows 6.1 / 6.7 / 11.1, 131,072 rows 29.7 / 21.9 / 20.2
 //   85 -> 64 -> 15           8,192 rows 5.0 / 5.2 / 11.7, 131,072 rows 14.9 / 11.5 / 17.5
-hipError_t launch_split(const RouteArgs& a, int hidden, int n_layers, int out_tiles, hipStream_t s) {
+// bias_last: the shape has no persistent kernel.
+hipError_t launch_split(const RouteArgs& a, int hidden, int n_layers, int out_tiles, bool bias_last, hipStream_t s) {
   const int64_t cus = a.persistent_blocks > 0 ? a.persistent_blocks : a.cus;
   const int size = a.n_total <= 32 * cus ? 0 : (a.n_total <= 64 * cus ? 1 : 2);
   SplitLaunch l{};
   switch (hidden) {
-    case 32: l = pick_nl<32>(n_layers, out_tiles, size); break;
-    case 64: l = pick_nl<64>(n_layers, out_tiles, size); break;
-    case 128: l = pick_nl<128>(n_layers, out_tiles, size); break;
-    case 256: l = pick_nl<256>(n_layers, out_tiles, size); break;
-    case 512: l = pick_nl<512>(n_layers, out_tiles, size); break;
+    case 32: l = pick_nl<32>(n_layers, out_tiles, bias_last, size); break;
+    case 64: l = pick_nl<64>(n_layers, out_tiles, bias_last, size); break;
+    case 128: l = pick_nl<128>(n_layers, out_tiles, bias_last, size); break;
+    case 256: l = pick_nl<256>(n_layers, out_tiles, bias_last, size); break;
+    case 512: l = pick_nl<512>(n_layers, out_tiles, bias_last, size); break;
     default: return hipErrorInvalidValue;
   }
   const unsigned blocks = (unsigned)(((int64_t)a.n_total + l.rows - 1) / l.rows);
