@@ -228,7 +228,8 @@ im_status im_pool_create_dual(const im_pool_desc* desc, const im_dual_net* net, 
  *            the row's q_idx is out of range (IM_ERR_QIDX is raised) or, in
  *            a dual-pathway pool, its role (IM_ERR_ROLE)
  *   logits   device fp32 [n_total x M*K] out (post logit-bias, pre-mask), or NULL
- * Argmax ties go to the lowest action index. */
+ * Argmax ties go to the lowest action index; a logit that is NaN is passed over,
+ * unless it is the lowest valid action's, which is then taken. */
 im_status im_route(im_pool* pool, const im_arrivals* arr, int32_t* actions, float* logits,
                    void* stream);
 

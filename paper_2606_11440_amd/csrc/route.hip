@@ -48,20 +48,42 @@ __device__ __forceinline__ void epilogue16(const RowCtx& c, const f32x4 (&acc)[A
   const uint64_t inv = (uint64_t)((int64_t)~c.amask >> (4 * q));
   const uint32_t mw[2] = {(uint32_t)inv, (uint32_t)(inv >> 32)};
   float zm[AT][4];
-  float best = __uint_as_float(0xffffffffu);
+  const uint32_t low = minus_inf();
+  float best = __uint_as_float(low);
 #pragma unroll
   for (int T = 0; T < AT; ++T) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) zm[T][r] = mask_logit(acc[T][r], bit_ones(mw[T >> 1], 16 * (T & 1) + r));
-    best = max3(best, zm[T][0], zm[T][1]);
-    best = max3(best, zm[T][2], zm[T][3]);
+    for (int r = 0; r < 4; ++r) zm[T][r] = mask_logit(acc[T][r], bit_ones(mw[T >> 1], 16 * (T & 1) + r), low);
+    best = maximum3(best, zm[T][0], zm[T][1]);
+    best = maximum3(best, zm[T][2], zm[T][3]);
   }
-  int32_t ba = 127;
 #pragma unroll
   for (int off = 16; off <= 32; off *= 2) {
     const float o = __shfl_xor(best, off, 64);
-    best = max3(best, o, o);
+    best = maximum3(best, o, o);
   }
+  // some row has a NaN among its valid logits (rare): best is kept NaN where the
+  // lowest valid action's is, and is the largest of the others elsewhere
+  if (ballot(best != best) != 0) {
+    const int first = __ffsll((unsigned long long)c.amask) - 1 - 4 * q;
+    float b = __uint_as_float(low);
+    int32_t first_nan = 0;
+#pragma unroll
+    for (int T = 0; T < AT; ++T)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        b = max3(b, zm[T][r], zm[T][r]);
+        first_nan |= first == 16 * T + r && zm[T][r] != zm[T][r];
+      }
+#pragma unroll
+    for (int off = 16; off <= 32; off *= 2) {
+      const float o = __shfl_xor(b, off, 64);
+      b = max3(b, o, o);
+      first_nan |= __shfl_xor(first_nan, off, 64);
+    }
+    if (!first_nan) best = b;
+  }
+  int32_t ba = 127;
 #pragma unroll
   for (int T = AT - 1; T >= 0; --T)
 #pragma unroll
@@ -69,8 +91,7 @@ __device__ __forceinline__ void epilogue16(const RowCtx& c, const f32x4 (&acc)[A
   ba += 4 * q;
 #pragma unroll
   for (int off = 16; off <= 32; off *= 2) ba = min(ba, __shfl_xor(ba, off, 64));
-  // -1 when no action is valid; the first valid one when every valid logit is NaN
-  if (ba >= 64) ba = __ffsll((unsigned long long)c.amask) - 1;
+  ba = argmax_of(ba, c.amask, best);
   if (a->rl) {
     const bool sample = a->greedy == 0;
     uint32_t id = 0;

@@ -312,11 +312,22 @@ __device__ __forceinline__ uint32_t request_id(KernArgs a, const RowCtx& c) {
 __device__ __forceinline__ uint32_t bit_ones(uint32_t w, int bit) {
   return (uint32_t)__builtin_amdgcn_sbfe((int)w, (uint32_t)bit, 1u);
 }
-// A logit, or a quiet NaN when `masked` is all ones; max3 and the compares
-// below pass over NaN operands, so a masked action needs no branch, and a valid
-// logit of -inf still differs from it.
-__device__ __forceinline__ float mask_logit(float z, uint32_t masked) {
-  return __uint_as_float(__float_as_uint(z) | masked);
+// A logit, or `low` (-inf) when `masked` is all ones (one v_bfi_b32).
+__device__ __forceinline__ float mask_logit(float z, uint32_t masked, uint32_t low) {
+  return __uint_as_float((low & masked) | (__float_as_uint(z) & ~masked));
+}
+// -inf in a register of the code around, not in one kept through the kernel's loop.
+constexpr uint32_t kMinusInf = 0xff800000u;
+__device__ __forceinline__ uint32_t minus_inf() {
+  uint32_t low = kMinusInf;
+  asm volatile("" : "+s"(low));
+  return low;
+}
+// Largest operand, NaN if one of them is.
+__device__ __forceinline__ float maximum3(float x, float y, float z) {
+  float r;
+  asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+  return r;
 }
 // Largest operand that is not NaN (one instruction; fmaxf would first
 // canonicalise each operand).
@@ -403,10 +414,63 @@ __device__ __forceinline__ void store_logits(KernArgs a, float* row, int act, fl
   }
 }
 
+// bit 32 T + 8 j + i of the words: action 32 T + 8 j + 4 g + i is masked
+struct MaskWords {
+  uint32_t w[2];
+};
+__device__ __forceinline__ MaskWords mask_words(uint64_t am, int g) {
+  const uint64_t inv = (uint64_t)((int64_t)~am >> (4 * g));
+  return {{(uint32_t)inv, (uint32_t)(inv >> 32)}};
+}
+constexpr int action_tiles(int at) { return at < 2 ? at : 2; }   // at most 64 actions; a third tile holds the value row only
+
+// The argmax is that of a scan over the valid actions which takes each one whose
+// logit exceeds the best one's: a NaN is passed over, unless the lowest valid
+// action's logit is NaN, which nothing exceeds. NaN is rare and dealt with after
+// the fact: where a row has one among its valid logits, this finds whether it is
+// the lowest valid action's and, with ARGMAX, the argmax of the others (both lanes
+// of the pair).
+struct NanScan {
+  bool first_nan;
+  int32_t ba;   // lowest action of the largest logit that is not NaN (where that is above -inf)
+  float best;   // that logit
+};
+template <int AT, bool ARGMAX>
+__device__ __forceinline__ NanScan nan_scan(uint64_t am, const f32x16 (&acc)[AT], int g) {
+  asm volatile("" : "+v"(am));   // the masked logits are formed again, not kept for this
+  const MaskWords mw = mask_words(am, g);
+  const int first = __ffsll((unsigned long long)am) - 1 - 4 * g;
+  const uint32_t low = minus_inf();
+  float best = __uint_as_float(low);
+  int32_t nan = 0, ba = 127;
+#pragma unroll
+  for (int T = 0; T < action_tiles(AT); ++T)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int act = 32 * T + 8 * (v >> 2) + (v & 3);
+      const float z = mask_logit(acc[T][v], bit_ones(mw.w[T], 8 * (v >> 2) + (v & 3)), low);
+      nan |= first == act && z != z;
+      if constexpr (ARGMAX) {
+        ba = z > best ? act : ba;
+        best = max3(best, z, z);
+      }
+    }
+  nan |= xshfl<32>(nan);
+  if constexpr (!ARGMAX) return {nan != 0, 127, 0.f};
+  ba += 4 * g;
+  int32_t x, y;
+  swap_halves<32>(as_int(best), x, y);
+  const float all = max3(__int_as_float(x), __int_as_float(y), __int_as_float(y));
+  ba = best == all ? ba : 127;
+  swap_halves<32>(ba, x, y);
+  return {nan != 0, x < y ? x : y, all};
+}
+
 // One 32-row tile's part of the outputs: lane (n, g) holds the actions 32 T +
 // 8 (v / 4) + 4 g + v % 4 of its row n. `am` is the row's action mask, `id` and
 // `e` its request id and env (RL sampling). best: the row's largest valid logit
-// (both lanes of the pair); ba, r, val: this lane's part of the argmax, the sums
+// (both lanes of the pair): NaN is passed over with RL outputs, where the sum of
+// the exponentials shows it, and propagates without; ba, r, val: this lane's part of the argmax, the sums
 // and the value row, to be joined with the other lane's.
 struct TileOut {
   float best;
@@ -418,23 +482,30 @@ template <int AT>
 __device__ __forceinline__ TileOut tile_out(KernArgs a, bool rl, uint64_t am, uint32_t id, int32_t e,
                                             const f32x16 (&acc)[AT], int g) {
   TileOut o;
-  // bit 32 T + 8 j + i: action 32 T + 8 j + 4 g + i is masked
-  const uint64_t inv = (uint64_t)((int64_t)~am >> (4 * g));
-  const uint32_t mw[2] = {(uint32_t)inv, (uint32_t)(inv >> 32)};
-  constexpr int AA = AT < 2 ? AT : 2;   // tiles with actions (at most 64; a third tile holds the value row only)
+  const MaskWords m = mask_words(am, g);
+  constexpr int AA = action_tiles(AT);
+  const uint32_t low = rl ? ~0u : minus_inf();   // what a masked logit becomes: NaN where NaN is passed over (one v_or_b32)
   float zm[AA][16];
-  float best = __uint_as_float(0xffffffffu);
+  float best = __uint_as_float(low);
 #pragma unroll
-  for (int T = 0; T < AA; ++T) {
+  for (int T = 0; T < AA; ++T)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) zm[T][v] = mask_logit(acc[T][v], bit_ones(mw[T], 8 * (v >> 2) + (v & 3)));
+    for (int v = 0; v < 16; ++v) zm[T][v] = mask_logit(acc[T][v], bit_ones(m.w[T], 8 * (v >> 2) + (v & 3)), low);
+  int32_t x, y;
+  if (rl) {   // uniform
 #pragma unroll
-    for (int v = 0; v < 16; v += 2) best = max3(best, zm[T][v], zm[T][v + 1]);
-  }
-  {
-    int32_t x, y;
+    for (int T = 0; T < AA; ++T)
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) best = max3(best, zm[T][v], zm[T][v + 1]);
     swap_halves<32>(as_int(best), x, y);
     best = max3(__int_as_float(x), __int_as_float(y), __int_as_float(y));
+  } else {
+#pragma unroll
+    for (int T = 0; T < AA; ++T)
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) best = maximum3(best, zm[T][v], zm[T][v + 1]);
+    swap_halves<32>(as_int(best), x, y);
+    best = maximum3(__int_as_float(x), __int_as_float(y), __int_as_float(y));
   }
   o.best = best;
   o.ba = 127;
@@ -460,7 +531,7 @@ __device__ __forceinline__ TileOut tile_out(KernArgs a, bool rl, uint64_t am, ui
       const int a0 = 32 * T + 8 * j;   // the lane pair's 8 actions: two Philox blocks
       const float z[4] = {acc[T][4 * j], acc[T][4 * j + 1], acc[T][4 * j + 2], acc[T][4 * j + 3]};
       if (T < AA && a0 < a->A) {        // uniform
-        const uint32_t mb = mw[T < AA ? T : 0] >> (8 * j);
+        const uint32_t mb = m.w[T < AA ? T : 0] >> (8 * j);
         if (sample) {
           const uint4 w = philox10(make_uint4(id, (uint32_t)e, (uint32_t)((a0 >> 2) + g), 0u), k0, k1);
           rl_block<true>(o.r, z, mb, best, a0 + 4 * g, w);
@@ -493,10 +564,17 @@ __device__ __forceinline__ void store_tile_logits(KernArgs a, int32_t r, int32_t
   }
 }
 
-// The action of a row from its joined argmax: -1 when no action is valid, the
-// first valid one when every valid logit is NaN.
-__device__ __forceinline__ int32_t argmax_of(int32_t ba, uint64_t am) {
-  return ba >= 64 ? __ffsll((unsigned long long)am) - 1 : ba;
+// The action of a row from its joined argmax and its largest logit: -1 when no
+// action is valid, the first valid one when none exceeds -inf, which masked
+// actions equal too (or when no logit is left beside NaN).
+__device__ __forceinline__ int32_t argmax_of(int32_t ba, uint64_t am, float best) {
+  return ba >= 64 || best == __uint_as_float(kMinusInf) ? __ffsll((unsigned long long)am) - 1 : ba;
+}
+// The action of a row with a NaN among its valid logits; with RL outputs (no
+// ARGMAX) only where its first valid one is NaN, which then is drawn too.
+template <bool ARGMAX>
+__device__ __forceinline__ void scan_store(KernArgs a, const RowCtx& c, const NanScan& f) {
+  if (!c.bad && (ARGMAX || f.first_nan)) a->actions[c.r] = argmax_of(f.first_nan ? 127 : f.ba, c.amask, f.best);
 }
 
 // Masked argmax over the lane pair (n, n + 32), logits store, action store (or
@@ -513,17 +591,29 @@ __device__ __forceinline__ void epilogue(const RowCtx& c, const f32x16 (&acc)[AT
   TileOut o = tile_out<AT>(a, rl, am, id, c.e, acc, g);
   int32_t x, y;
   swap_halves<32>(o.ba, x, y);
-  const int32_t ba = argmax_of(x < y ? x : y, c.amask);
+  const int32_t ba = argmax_of(x < y ? x : y, c.amask, o.best);
   if (rl) {
     auto other = [](float v) { return __int_as_float(xshfl<32>(as_int(v))); };
     rl_join(o.r, other(o.r.s), other(o.r.sz), other(o.r.bs), other(o.r.bz), xshfl<32>(o.r.ba));
     o.val += other(o.val);   // one lane of the pair holds row A
-    if (c.live && g == 0) rl_store(a, c, o.r, o.best, ba, o.val);
-  } else if (c.live && g == 0) {
-    a->actions[c.r] = c.bad ? -1 : ba;
-    if (c.bad) atomicOr(a->err, c.bad);
+  }
+  if (c.live && g == 0) {
+    if (rl) {
+      rl_store(a, c, o.r, o.best, ba, o.val);
+    } else {
+      a->actions[c.r] = c.bad ? -1 : ba;
+      if (c.bad) atomicOr(a->err, c.bad);
+    }
   }
   if (c.live && a->logits) store_tile_logits<AT>(a, c.r, c.bad, acc, g);
+  const float sign = rl ? o.r.s : o.best;
+  if (ballot(sign != sign) != 0) {
+    const NanScan f = nan_scan<AT, RL != 1>(c.amask, acc, g);
+    if (sign != sign && c.live && g == 0) {
+      if (rl) scan_store<false>(a, c, f);
+      else scan_store<true>(a, c, f);
+    }
+  }
 }
 
 // Two registers v0, v1 that hold tile 0's and tile 1's value in every lane pair:
@@ -561,9 +651,11 @@ __device__ __forceinline__ void epilogue64(const RowCtx& c, const f32x16 (&acc)[
     o[j] = tile_out<AT>(a, RL == 1, (uint64_t)(uint32_t)hi[j] << 32 | (uint32_t)lo[j], (uint32_t)id[j], e[j], acc[j], g);
   int32_t x, y;
   own_halves(o[0].ba, o[1].ba, x, y);
-  const int32_t ba = argmax_of(x < y ? x : y, am);
+  const float best = g ? o[1].best : o[0].best;
+  const int32_t ba = argmax_of(x < y ? x : y, am, best);
+  RlSums r;
+  float val = 0.f;
   if constexpr (RL == 1) {
-    RlSums r;
     auto meet = [](float v0, float v1, float& p, float& q) {
       int32_t s, t;
       own_halves(as_int(v0), as_int(v1), s, t);
@@ -578,18 +670,34 @@ __device__ __forceinline__ void epilogue64(const RowCtx& c, const f32x16 (&acc)[
     own_halves(o[0].r.ba, o[1].r.ba, r.ba, x);
     rl_join(r, s, sz, bs, bz, x);
     meet(o[0].val, o[1].val, v0, v1);   // one lane of the pair holds row A
-    if (c.live) rl_store(a, c, r, g ? o[1].best : o[0].best, ba, v0 + v1);
-  } else if (c.live) {
-    a->actions[c.r] = c.bad ? -1 : ba;
-    if (c.bad) atomicOr(a->err, c.bad);
+    val = v0 + v1;
+  }
+  if (c.live) {
+    if constexpr (RL == 1) {
+      rl_store(a, c, r, best, ba, val);
+    } else {
+      a->actions[c.r] = c.bad ? -1 : ba;
+      if (c.bad) atomicOr(a->err, c.bad);
+    }
   }
   if (a->logits) {
-    int32_t bad[2], r[2];
+    int32_t bad[2], row[2];
     spread(c.bad, bad);
-    spread(c.live ? c.r : -1, r);
+    spread(c.live ? c.r : -1, row);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      if (r[j] >= 0) store_tile_logits<AT>(a, r[j], bad[j], acc[j], g);
+      if (row[j] >= 0) store_tile_logits<AT>(a, row[j], bad[j], acc[j], g);
+  }
+  const float sign = RL == 1 ? r.s : best;
+  if (ballot(sign != sign) != 0) {
+    // the scan of both tiles, for the row this lane owns
+    uint64_t m = c.amask;
+    asm volatile("" : "+v"(m));
+    spread((int32_t)(uint32_t)m, lo);
+    spread((int32_t)(m >> 32), hi);
+    const NanScan f0 = nan_scan<AT, RL == 0>((uint64_t)(uint32_t)hi[0] << 32 | (uint32_t)lo[0], acc[0], g);
+    const NanScan f1 = nan_scan<AT, RL == 0>((uint64_t)(uint32_t)hi[1] << 32 | (uint32_t)lo[1], acc[1], g);
+    if (sign != sign && c.live) scan_store<RL == 0>(a, c, g ? f1 : f0);
   }
 }
 

@@ -1,13 +1,15 @@
 """GPU: the masked argmax and the draw of the route kernels on logits chosen
 exactly (a policy with zero weights, whose logits are its biases): ties, signed
 zeros, the lowest finite value, infinities and NaN, with every model enabled
-and with some disabled. The greedy action is the lowest valid action whose
-logit is the largest one that is not NaN (the lowest valid one when all are
-NaN, -1 when none is valid); a drawn action is always valid and never has
-probability 0 beside finite logits."""
+and with some disabled. The greedy action is the oracle's: a scan over the valid
+actions that takes each whose logit exceeds the best one's, so NaN is passed
+over but for the lowest valid action's, which nothing exceeds (-1 when none is
+valid); a drawn action is always valid, follows the same rule where logits are
+NaN and never has probability 0 beside finite logits."""
 import numpy as np
 import pytest
 
+import oracle
 import workload
 from gpu_util import need_gpu
 
@@ -26,6 +28,8 @@ def _logits(A):
          np.where(np.arange(A) == A // 2, INF, 0.0), r.normal(size=A)]
     z[-1][r.integers(0, A, 3)] = NAN
     z.append(np.round(r.normal(size=A) * 2) / 2)   # several ties
+    z.append(r.permutation(A) * 1e-41)             # subnormal
+    z += [np.where(np.arange(A) % 2, r.normal(size=A), NAN), np.where(np.arange(A) % 2, -INF, NAN)]
     return [np.asarray(x, np.float32) for x in z]
 
 
@@ -39,16 +43,21 @@ def test_exact_logits(dtype, H, M, K, blocks):
                                feat_dim=ed + 4 * M + 1, widths=[H, H, A])
     emb = torch.zeros((8, ed), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
     dev = lambda x, t: torch.as_tensor(x, dtype=t).cuda()  # noqa: E731
+    rows = dict(offsets=np.array([0, n, 2 * n], np.int32), q_idx=np.arange(2 * n, dtype=np.int32) % 8,
+                budget=np.full(2 * n, 50, np.int16), base_svc=np.full(2 * n, 3, np.int16))
     arr = P.make_arrivals(dev([0, n, 2 * n], torch.int32), dev(np.arange(2 * n) % 8, torch.int32),
                           dev(np.full(2 * n, 50), torch.int16), dev(np.full(2 * n, 3), torch.int16))
     for z in _logits(A):
         W = [np.zeros((H, ed + 4 * M + 1), np.float32), np.zeros((H, H), np.float32), np.zeros((A, H), np.float32)]
         pool = P.Pool(cfg, W, [np.zeros(H, np.float32), np.zeros(H, np.float32), z], emb,
                       np.full((E, M), 2, np.int32))
+        orc = oracle.Oracle(cfg, W, [np.zeros(H, np.float32), np.zeros(H, np.float32), z],
+                            np.zeros((8, ed)), np.full((E, M), 2, np.int32))
         pool.set_launch(blocks)
         off = (0, M - 1)   # models disabled in env 1
         for m in off:
             pool.set_enabled(1, m, 0)
+            orc.set_enabled(1, m, 0)
         act = torch.full((2 * n,), -7, dtype=torch.int32, device="cuda")
         pool.route(arr, act)
         drawn = act.clone()
@@ -57,17 +66,20 @@ def test_exact_logits(dtype, H, M, K, blocks):
         greedy = act.clone()
         pool.route_sample(arr, 5, greedy, greedy=True)
         torch.cuda.synchronize()
+        scan, _ = orc.route(rows)
         valid = np.ones((E, A), bool)
         for m in off:
             valid[1, m * K:(m + 1) * K] = False
         for e in range(E):
             got = act[e * n:(e + 1) * n].cpu().numpy()
-            ok = valid[e] & ~np.isnan(z)
-            want = int(np.nonzero(ok & (z == z[ok].max()))[0][0]) if ok.any() else int(np.nonzero(valid[e])[0][0])
+            ok, first = valid[e] & ~np.isnan(z), int(np.nonzero(valid[e])[0][0])
+            want = first if np.isnan(z[first]) else int(np.nonzero(ok & (z == z[ok].max()))[0][0])
+            assert (scan[e * n:(e + 1) * n] == want).all()
             assert (got == want).all(), (z, e, want, got[:4])
             assert (greedy[e * n:(e + 1) * n].cpu().numpy() == want).all()
             d = drawn[e * n:(e + 1) * n].cpu().numpy()
             assert valid[e][d].all()
+            assert (d == first).all() if np.isnan(z[first]) else not np.isnan(z[d]).any()
             if np.isfinite(z[valid[e]]).any() and not np.isnan(z).any() and not np.isposinf(z).any():
                 assert not np.isneginf(z[d]).any()
             if np.isfinite(z).all():
