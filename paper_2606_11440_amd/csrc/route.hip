@@ -1404,7 +1404,8 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
   // from L2 per MFMA. us per launch at 1 / 2 tiles: 86 -> 256 -> 256 -> 15 at
   // 4,096 rows 12.5 / 17.8, 8,192 rows 21.2 / 18.4, 16,384 rows 37.8 / 32.7;
   // 449 -> 256 -> 64 at 4,096 rows 22.6 / 30.8, 16,384 rows 58.0 / 49.4.
-  const int nr = a.n_total <= 16 * a.cus ? 1 : 2;
+  // (The count of compute units is 0 where the device did not tell it.)
+  const int nr = a.cus <= 0 || a.n_total <= 16 * a.cus ? 1 : 2;
   RouteKernel k = n_layers == 2 ? pick<2>(hidden, out_tiles, nr) : pick<3>(hidden, out_tiles, nr);
   // With two, the rows past the last whole round of 32-row blocks (one per
   // compute unit) go in 16-row blocks if these fit one per compute unit: a few

@@ -1,0 +1,42 @@
+"""Host side of the C ABI on a machine without a GPU: a small program stands in
+for the runtime (memory from the host, kernels not run) and prints the launches
+of a scenario with their grids and the device current at each."""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2606_11440_amd", "libinframind.so")
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if not os.path.exists(LIB):
+        from paper_2606_11440_amd import build
+        build.build()
+    out = str(tmp_path_factory.mktemp("host") / "host_calls")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-rdynamic", "-o", out,
+                           os.path.join(ROOT, "tests", "host_calls.cpp"), "-ldl"])
+    return out
+
+
+def run(program, *scenario):
+    r = subprocess.run([program, LIB, *scenario], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-2000:])
+    return r.stdout
+
+
+def launches(text):
+    """(kernel, grid, block, device) of each launch."""
+    found = re.findall(r"launch (\S+) grid (\d+) block (\d+) device (\d+)", text)
+    return [(k, int(g), int(b), int(d)) for k, g, b, d in found]
+
+
+def test_no_compute_unit_count(program):
+    """A failed query of the compute units leaves a pool that routes."""
+    text = run(program, "no_cu_count")
+    got = launches(text)
+    assert len(got) == 12 and all("route" in k for k, *_ in got), text
+    assert all(g >= 1 for _, g, _, _ in got)
