@@ -122,6 +122,29 @@ im_status hip_fail(im_pool* p, hipError_t e, const char* what) {
     if (_e != hipSuccess) return hip_fail((p), _e, #call); \
   } while (0)
 
+// Makes a pool's device the current one while a call works on the pool with
+// launches and memory of its own; the caller's is current again afterwards.
+class OnDevice {
+ public:
+  explicit OnDevice(int device) {
+    err = hipGetDevice(&was_);
+    if (err == hipSuccess && was_ != device) {
+      err = hipSetDevice(device);
+      moved_ = err == hipSuccess;
+    }
+  }
+  ~OnDevice() {
+    if (moved_) (void)hipSetDevice(was_);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+  hipError_t err;
+
+ private:
+  int was_ = 0;
+  bool moved_ = false;
+};
+
 // fp32 -> bf16 bits, round to nearest even (NaN kept quiet).
 uint16_t to_bf16(float f) {
   uint32_t u;
@@ -959,6 +982,8 @@ im_status im_read_state(im_pool* p, int32_t env_begin, int32_t env_count, int32_
   if (!p) return fail(nullptr, IM_EINVAL, "pool is NULL");
   if (env_begin < 0 || env_count < 0 || (int64_t)env_begin + env_count > p->d.n_envs)
     return fail(p, IM_EINVAL, "env range out of bounds");
+  const OnDevice on(p->device);
+  IM_HIP(p, on.err);
   IM_HIP(p, hipDeviceSynchronize());
   const int M = p->d.n_models, S = p->S, qcap = p->d.queue_cap, A = p->A;
   if (env_count == 0) {
@@ -1187,6 +1212,8 @@ static im_status write_state_impl(im_pool* p, int32_t env_begin, int32_t env_cou
     ec[EC * e + im::E_Q_DONE] = envs[e].q_done;
     ec[EC * e + im::E_Q_MET] = envs[e].q_met;
   }
+  const OnDevice on(p->device);
+  IM_HIP(p, on.err);
   IM_HIP(p, hipDeviceSynchronize());
   if (EMc) {
     IM_HIP(p, hipMemcpy(p->ms + em0, recs.data(), EMc * sizeof(ModelRec), hipMemcpyHostToDevice));

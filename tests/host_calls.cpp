@@ -139,6 +139,26 @@ static im_arrivals arrivals(int n, int E) {
   return a;
 }
 
+// Reads envs [e0, e0 + n) and writes them back.
+static void read_and_write(im_pool* p, const Shape& s, int e0, int n, bool write) {
+  std::vector<im_env_state> envs(n);
+  std::vector<im_model_state> models((size_t)n * s.M);
+  std::vector<im_slot> slots((size_t)n * s.M * s.slots);
+  std::vector<im_entry> queues((size_t)n * s.M * s.qcap);
+  std::vector<int64_t> hist((size_t)n * s.M * s.K);
+  int32_t t = 0;
+  need(CALL(im_read_state)(p, e0, n, &t, envs.data(), models.data(), slots.data(), queues.data(), hist.data()),
+       "im_read_state");
+  if (!write) return;
+  for (im_model_state& m : models) {
+    m = im_model_state{};
+    m.capacity = m.enabled = 1;
+  }
+  for (im_slot& x : slots) x = im_slot{-1, 0, 0, 0};
+  need(CALL(im_write_state)(p, e0, n, 0, envs.data(), models.data(), slots.data(), queues.data(), hist.data()),
+       "im_write_state");
+}
+
 int main(int argc, char** argv) {
   if (argc < 3) return 2;
   const std::string what = argv[2];
@@ -146,6 +166,18 @@ int main(int argc, char** argv) {
   if (!g_lib) {
     printf("%s\n", dlerror());
     return 2;
+  }
+  if (what == "other_device") {   // a pool of device 0, used while device 1 is current
+    const Shape s{3, 2, 2, 8, 2, 64, 2, IM_F32, 1};
+    im_pool* p = make(s);
+    g_device = 1;
+    g_log = true;
+    read_and_write(p, s, 0, 3, true);
+    printf("after device %d\n", g_device);
+    g_log = false;
+    g_device = 0;
+    CALL(im_destroy)(p);
+    return 0;
   }
   if (what == "no_cu_count") {   // the compute units are not known
     g_cus = -1;

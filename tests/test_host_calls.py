@@ -40,3 +40,14 @@ def test_no_compute_unit_count(program):
     got = launches(text)
     assert len(got) == 12 and all("route" in k for k, *_ in got), text
     assert all(g >= 1 for _, g, _, _ in got)
+
+
+def test_state_calls_run_on_the_pools_device(program):
+    """Reading and restoring a pool's state while another device is current works
+    on the pool's device, and leaves the caller's current."""
+    text = run(program, "other_device")
+    got = launches(text)
+    for name in ("export_kernel", "snapshot_kernel", "dual_recount_kernel"):
+        assert any(name in k for k, *_ in got), text
+    assert "device 1" not in text.replace("after device 1", ""), text
+    assert text.endswith("after device 1\n")
