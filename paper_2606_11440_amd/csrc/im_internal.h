@@ -187,8 +187,8 @@ struct SchedArgs {
 // schedule step, last [2] totals at the previous update, lambda device in/out.
 hipError_t launch_dual_update(const int64_t* shards, int64_t* last, double eta, double lambda_max, double* lambda,
                               hipStream_t s);
-// The shards from the counters (after the host wrote those).
-hipError_t launch_dual_recount(const SchedArgs& a, bool chain, hipStream_t s);
+// The shards of envs [e0, e0 + ne) from the counters (after the host wrote those envs').
+hipError_t launch_dual_recount(const SchedArgs& a, bool chain, int e0, int ne, hipStream_t s);
 bool route_supported(int dtype, int hidden, int n_layers, int out_tiles);
 bool dual_supported(int embed_dim, int out_rows);
 // Role projections of the dual-pathway executor: out[r][tile][g][16] =

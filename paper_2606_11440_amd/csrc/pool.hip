@@ -1239,7 +1239,7 @@ static im_status write_state_impl(im_pool* p, int32_t env_begin, int32_t env_cou
     IM_HIP(p, hipMemcpy(p->hist + (size_t)env_begin * A, hist, (size_t)env_count * A * 8, hipMemcpyHostToDevice));
   }
   IM_HIP(p, im::launch_snapshot(sched_args(p), env_begin, env_count, nullptr));
-  IM_HIP(p, im::launch_dual_recount(sched_args(p), p->chains, nullptr));
+  IM_HIP(p, im::launch_dual_recount(sched_args(p), p->chains, env_begin, env_count, nullptr));
   IM_HIP(p, hipDeviceSynchronize());
   p->t = tick;
   return IM_OK;

@@ -1252,21 +1252,37 @@ __global__ __launch_bounds__(256) void dual_update_kernel(const int64_t* shards,
   }
 }
 
-// The running totals from the counters, after a state restore: one thread per shard.
-__global__ void dual_recount_kernel(SchedArgs a, bool chain) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= kDualShards) return;
+// The running totals of the shards that envs [e0, e0 + blocks) fall into, from the
+// counters, after a state restore: a block per shard, over the counters of all the
+// shard's envs. Restoring one of 65,536 envs of 8 models takes 143 us, as without the
+// recount; with every shard recounted, a thread each, it took 245.
+__global__ __launch_bounds__(256) void dual_recount_kernel(SchedArgs a, bool chain, int32_t e0) {
+  __shared__ int64_t part[2][4];
+  const int i = (int)((e0 + (int64_t)blockIdx.x) % kDualShards);
+  const int64_t envs = i < a.E ? (a.E - i - 1) / kDualShards + 1 : 0;
   int64_t n = 0, c = 0;
-  for (int64_t e = i; e < a.E; e += kDualShards) {
-    for (int m = 0; m < a.M; ++m) {
-      const int64_t* k = a.cnt + (e * a.M + m) * C_NUM;
-      if (!chain) n += k[C_COMPLETED];
-      c += k[C_COST_Q16];
-    }
-    if (chain) n += a.env_cnt[e * kEnvCnt + E_Q_DONE];
+  for (int64_t j = threadIdx.x; j < envs * a.M; j += 256) {
+    const int64_t e = i + j / a.M * kDualShards;
+    const int64_t* k = a.cnt + (e * a.M + j % a.M) * C_NUM;
+    if (!chain) n += k[C_COMPLETED];
+    c += k[C_COST_Q16];
   }
-  a.dual_shards[2 * i] = n;
-  a.dual_shards[2 * i + 1] = c;
+  if (chain)
+    for (int64_t j = threadIdx.x; j < envs; j += 256) n += a.env_cnt[(i + j * kDualShards) * kEnvCnt + E_Q_DONE];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    n += shfl_xor(n, m);
+    c += shfl_xor(c, m);
+  }
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    part[0][w] = n;
+    part[1][w] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  a.dual_shards[2 * i] = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+  a.dual_shards[2 * i + 1] = part[1][0] + part[1][1] + part[1][2] + part[1][3];
 }
 
 }  // namespace
@@ -1277,8 +1293,10 @@ hipError_t launch_dual_update(const int64_t* shards, int64_t* last, double eta, 
   return hipGetLastError();
 }
 
-hipError_t launch_dual_recount(const SchedArgs& a, bool chain, hipStream_t s) {
-  hipLaunchKernelGGL(dual_recount_kernel, dim3(kDualShards / 64), dim3(64), 0, s, a, chain);
+hipError_t launch_dual_recount(const SchedArgs& a, bool chain, int e0, int ne, hipStream_t s) {
+  if (ne <= 0) return hipSuccess;
+  const unsigned blocks = (unsigned)(ne < kDualShards ? ne : kDualShards);
+  hipLaunchKernelGGL(dual_recount_kernel, dim3(blocks), dim3(256), 0, s, a, chain, e0);
   return hipGetLastError();
 }
 

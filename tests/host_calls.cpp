@@ -141,11 +141,11 @@ static im_arrivals arrivals(int n, int E) {
 
 // Reads envs [e0, e0 + n) and writes them back.
 static void read_and_write(im_pool* p, const Shape& s, int e0, int n, bool write) {
-  std::vector<im_env_state> envs(n);
-  std::vector<im_model_state> models((size_t)n * s.M);
-  std::vector<im_slot> slots((size_t)n * s.M * s.slots);
-  std::vector<im_entry> queues((size_t)n * s.M * s.qcap);
-  std::vector<int64_t> hist((size_t)n * s.M * s.K);
+  std::vector<im_env_state> envs(n + 1);
+  std::vector<im_model_state> models((size_t)(n + 1) * s.M);
+  std::vector<im_slot> slots((size_t)(n + 1) * s.M * s.slots);
+  std::vector<im_entry> queues((size_t)(n + 1) * s.M * s.qcap);
+  std::vector<int64_t> hist((size_t)(n + 1) * s.M * s.K);
   int32_t t = 0;
   need(CALL(im_read_state)(p, e0, n, &t, envs.data(), models.data(), slots.data(), queues.data(), hist.data()),
        "im_read_state");
@@ -197,6 +197,18 @@ int main(int argc, char** argv) {
         CALL(im_destroy)(p);
       }
     }
+    return 0;
+  }
+  if (what == "restore") {   // parts of a pool restored
+    const Shape s{3000, 2, 2, 1, 1, 64, 2, IM_F32, 1};
+    im_pool* p = make(s);
+    for (const int n : {0, 1, 3, 1024, 2000}) {
+      printf("envs %d\n", n);
+      g_log = true;
+      read_and_write(p, s, 1000, n, true);
+      g_log = false;
+    }
+    CALL(im_destroy)(p);
     return 0;
   }
   printf("no scenario %s\n", what.c_str());

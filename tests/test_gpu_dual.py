@@ -95,3 +95,44 @@ def test_dual_running_totals_follow_the_counters(E):
             assert lam.item() == want, (t, lam.item(), want)
     assert last[0] > 0 and pool.error() == 0
     pool.close()
+
+
+@pytest.mark.parametrize("steps", [1, 3])
+@pytest.mark.parametrize("E,first,count", [(1, 0, 1), (300, 299, 1), (2100, 1000, 100), (2100, 5, 1), (2100, 0, 2100),
+                                           (2100, 700, 1300)])
+def test_dual_totals_after_a_partial_restore(E, first, count, steps):
+    """Envs restored with other counters (a range that wraps round the shards of
+    the running totals, one env, more envs than shards): the next update takes
+    exactly the difference, and the other envs' totals stay."""
+    torch = need_gpu()
+    import paper_2606_11440_amd as P
+    cfg = workload.configs.get("c2", E=E, M=3, K=1, T=12, lam=3.0, qcap=32, embed_dim=64, feat_dim=77,
+                               widths=[64, 3], svc_mu=0.0, max_steps=steps)
+    W, b = workload.gen.weights(cfg, 3, 0.1)
+    emb = torch.zeros((16, 64), dtype=torch.bfloat16, device="cuda")
+    pool = P.Pool(cfg, W, b, emb, workload.gen.capacities(cfg, 3))
+    counts = workload.gen.counts(cfg, 3)
+    lam, want, last = _lam(torch, 0.4), 0.4, (0, 0)
+    for t in range(cfg["T"]):
+        pool.tick(P.device_arrivals(workload.gen.tick(cfg, 3, t, counts[t], 16)))
+        if t in (5, 9):
+            s = pool.state(first, count)
+            s["completed"] += 2 + np.arange(count)[:, None] % 3
+            s["cost_q16"] += 70000 * (1 + np.arange(count)[:, None] % 5)
+            s["q_done"] += 1 + np.arange(count) % 2
+            if steps > 1:
+                pool.write_chain_state(first, s, pool.chain_state(first, count))
+            else:
+                pool.write_state(first, s)
+        if t in (4, 5, 9, 11):
+            pool.dual_update(0.05, 2.0, lam)
+            s = pool.state()
+            tot = (int((s["q_done"] if steps > 1 else s["completed"]).sum()), int(s["cost_q16"].sum()))
+            dn, dc = tot[0] - last[0], tot[1] - last[1]
+            last = tot
+            if dn > 0:
+                want = min(max(want + 0.05 * (dc / (65536.0 * dn) - 1.0), 0.0), 2.0)
+            torch.cuda.synchronize()
+            assert lam.item() == want, (t, lam.item(), want)
+    assert last[0] > 0 and pool.error() == 0
+    pool.close()

@@ -51,3 +51,11 @@ def test_state_calls_run_on_the_pools_device(program):
         assert any(name in k for k, *_ in got), text
     assert "device 1" not in text.replace("after device 1", ""), text
     assert text.endswith("after device 1\n")
+
+
+def test_restore_recounts_what_it_touched(program):
+    """The running totals of the dual update (1,024 shards, env e in shard e mod
+    1,024) are recounted for the restored envs' shards only, a block each."""
+    parts = run(program, "restore").split("envs ")[1:]
+    got = {int(t.split("\n")[0]): [g for k, g, _, _ in launches(t) if "dual_recount" in k] for t in parts}
+    assert got == {0: [], 1: [1], 3: [3], 1024: [1024], 2000: [1024]}
