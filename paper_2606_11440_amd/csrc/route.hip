@@ -469,7 +469,34 @@ __device__ __forceinline__ void f32s_block(const RouteArgs& a, int32_t row0, f32
     epilogue16<AT>(c[j], out, q);
   }
 }
-// NR 2: the first a.pair_blocks blocks take 32 rows, the others 16.
+// The blocks that n rows take on a device of `cus` compute units (0: not known):
+// `pairs` of two 16-row tiles, then `singles` of one.
+//
+// One tile per block while the blocks fit one per compute unit (a block's latency
+// bounds the launch), else two, which halves the weight bytes from L2 per MFMA. us
+// per launch at 1 / 2 tiles: 86 -> 256 -> 256 -> 15 at 4,096 rows 12.5 / 17.8,
+// 8,192 rows 21.2 / 18.4, 16,384 rows 37.8 / 32.7; 449 -> 256 -> 64 at 4,096 rows
+// 22.6 / 30.8, 16,384 rows 58.0 / 49.4.
+// With two, the rows past the last whole round of 32-row blocks (one per compute
+// unit) go in 16-row blocks if these fit one per compute unit: a few rows more than
+// whole rounds then cost their units half a block. us per launch with 32-row blocks
+// only / with the tail in 16-row blocks, 86 -> 256 -> 256 -> 15: 8,250 rows 30.9 /
+// 26.2, 16,400 rows 43.0 / 37.5, 20,480 rows 45.6 / 40.4, 33,000 rows 74.7 / 66.1;
+// 54 -> 64 -> 15: 16,400 rows 7.2 / 6.7. Past half a round the tail would need two
+// 16-row blocks on some units, which a 32-row block does in less time.
+struct F32Blocks {
+  int32_t pairs, singles;
+};
+__host__ __device__ inline F32Blocks f32_blocks(int32_t n, int32_t cus) {
+  if (cus <= 0 || n <= 16 * cus) return {0, (n + 15) / 16};
+  const int32_t rest = n % (32 * cus);
+  if (rest > 16 * cus) return {(n + 31) / 32, 0};
+  return {(n - rest) / 32, (rest + 15) / 16};
+}
+
+// NR 2: the first a.pair_blocks blocks take 32 rows, the others 16. Chain pools:
+// the row count is known here only, and the blocks are shared out by it (the
+// launch's grid covers every count up to the bound).
 template <int H, int NL, int AT, int NR>
 __global__ __launch_bounds__(256) void route_f32s(RouteArgs a_in) {
   // chain pools: the tick's row count is on the device
@@ -479,10 +506,13 @@ __global__ __launch_bounds__(256) void route_f32s(RouteArgs a_in) {
   const int32_t b = (int32_t)blockIdx.x;
   if constexpr (NR == 1) {
     f32s_block<H, NL, AT, 1>(a, 16 * b, hs);
-  } else if (b < a.pair_blocks) {   // uniform
-    f32s_block<H, NL, AT, 2>(a, 32 * b, hs);
   } else {
-    f32s_block<H, NL, AT, 1>(a, 16 * (a.pair_blocks + b), hs);
+    const int32_t pairs = a_in.n_total_dev ? f32_blocks(a.n_total, a.cus).pairs : a.pair_blocks;
+    if (b < pairs) {   // uniform
+      f32s_block<H, NL, AT, 2>(a, 32 * b, hs);
+    } else {
+      f32s_block<H, NL, AT, 1>(a, 16 * (pairs + b), hs);
+    }
   }
 }
 
@@ -1399,33 +1429,20 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
     }
   }
   if (dtype == IM_BF16) return launch_split(a, hidden, n_layers, out_tiles, !persistent, s);
-  // One 16-row tile per block while the blocks fit one per compute unit (a
-  // block's latency bounds the launch), else two, which halves the weight bytes
-  // from L2 per MFMA. us per launch at 1 / 2 tiles: 86 -> 256 -> 256 -> 15 at
-  // 4,096 rows 12.5 / 17.8, 8,192 rows 21.2 / 18.4, 16,384 rows 37.8 / 32.7;
-  // 449 -> 256 -> 64 at 4,096 rows 22.6 / 30.8, 16,384 rows 58.0 / 49.4.
-  // (The count of compute units is 0 where the device did not tell it.)
+  const F32Blocks f32 = f32_blocks(a.n_total, a.cus);
   const int nr = a.cus <= 0 || a.n_total <= 16 * a.cus ? 1 : 2;
   RouteKernel k = n_layers == 2 ? pick<2>(hidden, out_tiles, nr) : pick<3>(hidden, out_tiles, nr);
-  // With two, the rows past the last whole round of 32-row blocks (one per
-  // compute unit) go in 16-row blocks if these fit one per compute unit: a few
-  // rows more than whole rounds then cost their units half a block. us per
-  // launch with 32-row blocks only / with the tail in 16-row blocks, 86 -> 256 ->
-  // 256 -> 15: 8,250 rows 30.9 / 26.2, 16,400 rows 43.0 / 37.5, 20,480 rows 45.6 /
-  // 40.4, 33,000 rows 74.7 / 66.1; 54 -> 64 -> 15: 16,400 rows 7.2 / 6.7. Past half
-  // a round the tail would need two 16-row blocks on some units, which a 32-row
-  // block does in less time.
   RouteArgs f = a;
-  unsigned blocks;
+  f.pair_blocks = f32.pairs;
+  unsigned blocks = (unsigned)(f32.pairs + f32.singles);
   if (hidden % 64 != 0) {
     blocks = (unsigned)((a.n_total + 63) / 64);   // 4 waves of 16 rows
-  } else if (nr == 1) {
-    blocks = (unsigned)((a.n_total + 15) / 16);
-  } else {
-    const int round = 32 * a.cus, rest = a.n_total % round;
-    const bool tail = rest <= 16 * a.cus;
-    f.pair_blocks = tail ? (a.n_total - rest) / 32 : (a.n_total + 31) / 32;
-    blocks = (unsigned)(f.pair_blocks + (tail ? (rest + 15) / 16 : 0));
+  } else if (a.n_total_dev && nr == 2) {
+    // Chain pools: whole rounds of blocks, which is the most that any row count up
+    // to the bound takes. us per im_route, rows build included, blocks by the bound /
+    // by the rows: 86 -> 256 -> 256 -> 15, 1,561 rows of at most 41,984, 26.3 / 20.2;
+    // 405 -> 256 -> 256 -> 15, 1,711 rows of as many, 39.1 / 27.3.
+    blocks = (unsigned)(a.cus * ((a.n_total - 1) / (32 * a.cus) + 1));
   }
   hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, f);
   return hipGetLastError();

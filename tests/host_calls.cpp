@@ -211,6 +211,19 @@ int main(int argc, char** argv) {
     CALL(im_destroy)(p);
     return 0;
   }
+  if (what == "chain_grid") {   // E models slots arrivals hidden cus
+    const int E = atoi(argv[3]), n = atoi(argv[6]);
+    g_cus = atoi(argv[8]);
+    const Shape s{E, atoi(argv[4]), 1, 1, atoi(argv[5]), atoi(argv[7]), 3, IM_F32, 3};
+    im_pool* p = make(s);
+    std::vector<int32_t> act((size_t)n + E * s.M * s.slots);
+    const im_arrivals a = arrivals(n, E);
+    g_log = true;
+    need(CALL(im_route)(p, &a, act.data(), nullptr, nullptr), "im_route");
+    g_log = false;
+    CALL(im_destroy)(p);
+    return 0;
+  }
   printf("no scenario %s\n", what.c_str());
   return 2;
 }

@@ -59,3 +59,29 @@ def test_restore_recounts_what_it_touched(program):
     parts = run(program, "restore").split("envs ")[1:]
     got = {int(t.split("\n")[0]): [g for k, g, _, _ in launches(t) if "dual_recount" in k] for t in parts}
     assert got == {0: [], 1: [1], 3: [3], 1024: [1024], 2000: [1024]}
+
+
+def f32_blocks(n, cus):
+    """(32-row blocks, 16-row blocks) of the fp32 route for n rows."""
+    if n <= 16 * cus:
+        return 0, -(-n // 16)
+    rest = n % (32 * cus)
+    if rest > 16 * cus:
+        return -(-n // 32), 0
+    return (n - rest) // 32, -(-rest // 16)
+
+
+@pytest.mark.parametrize("E,M,slots,n,hidden,cus", [(4, 2, 2, 1, 64, 8), (16, 2, 4, 1, 64, 8), (8, 2, 8, 0, 64, 8),
+                                                    (8, 2, 8, 1, 128, 8), (30, 3, 8, 47, 256, 8), (9, 1, 1, 600, 64, 4),
+                                                    (40, 3, 5, 40, 64, 3), (5, 1, 1, 2, 64, 256)])
+def test_chain_grid_covers_every_row_count(program, E, M, slots, n, hidden, cus):
+    """A chain pool's row count is known on the device only: the fp32 route's grid
+    has the blocks of every count up to the bound, and they cover the rows."""
+    text = run(program, "chain_grid", *map(str, (E, M, slots, n, hidden, cus)))
+    grid = next(g for k, g, _, _ in launches(text) if "route_f32" in k)
+    bound = n + E * M * slots
+    for rows in range(bound + 1):
+        pairs, singles = f32_blocks(rows, cus)
+        assert pairs + singles <= grid
+        assert 32 * pairs + 16 * singles >= rows and 32 * pairs <= rows + 31
+    assert grid <= max(cus * -(-bound // (32 * cus)), -(-bound // 16))
