@@ -388,11 +388,13 @@ def im_read_state(pool, env_begin: int, env_count: int, M: int, A: int, S: int, 
     md = models.reshape(E, M)
     qarr = None
     if with_queues:
-        w = queues.view(np.int32).reshape(E, M, qcap, 4)   # key, id, t_arr, svc | budget << 16
-        qarr = np.empty((E, M, qcap, 5), np.int32)
-        qarr[..., :3] = w[..., :3]
-        np.bitwise_and(w[..., 3], 0xffff, out=qarr[..., 3])
-        np.right_shift(w[..., 3], 16, out=qarr[..., 4])
+        # key, id, t_arr, svc | budget << 16: a column at a time, in long runs
+        w, q5 = queues.view(np.int32).reshape(-1, 4), np.empty((E * M * qcap, 5), np.int32)
+        for i in range(3):
+            q5[:, i] = w[:, i]
+        np.bitwise_and(w[:, 3], 0xffff, out=q5[:, 3])
+        np.right_shift(w[:, 3], 16, out=q5[:, 4])
+        qarr = q5.reshape(E, M, qcap, 5)
     sl = slots.reshape(E, M, S)
     sarr = np.stack([sl["id"], sl["t_arr"], sl["rem"], sl["budget"]], axis=-1).astype(np.int32)
     out = dict(t=int(tick.value), next_id=envs["next_id"].copy(), arrived=envs["arrived"].copy(),
