@@ -146,19 +146,24 @@ def _check(status, pool=None):
     return status
 
 
-_current = None   # torch's (raw stream of a device, current device) accessors
+_current = None   # (stream handle of a device, current device) accessors
 
 
 def _stream(stream):
     """The handle of `stream`, or of torch's current stream on the current
-    device (its raw handle: building the Stream object costs more than a launch)."""
+    device (its raw handle: building the Stream object costs more than a launch;
+    a torch without the raw accessors gives it through the object)."""
     if stream is not None:
         return int(stream)
     global _current
     if _current is None:
         import torch
         torch.cuda.init()
-        _current = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        if raw is None or device is None:
+            raw, device = (lambda d: torch.cuda.current_stream(d).cuda_stream), torch.cuda.current_device
+        _current = (raw, device)
     return _current[0](_current[1]())
 
 
