@@ -996,8 +996,10 @@ im_status im_read_state(im_pool* p, int32_t env_begin, int32_t env_count, int32_
   constexpr size_t kPad = 8 * 64;              // the parts start at multiples of 64 bytes
   constexpr size_t room = kExportBytes - kPad;
   const size_t all = env_count * (env_rest + (queues ? M * row_queue : 0));
-  const size_t want = kPad + std::min(all, room);
+  size_t want = kPad + std::min(all, room);
   if (p->stage_bytes < want) {
+    // at least twice as much as before: reads of slowly growing ranges allocate (20 to 75 us) a few times in all
+    want = std::min(std::max(want, 2 * p->stage_bytes), kPad + room);
     if (p->stage) IM_HIP(p, hipHostFree(p->stage));
     p->stage = nullptr;
     p->stage_bytes = 0;

@@ -224,6 +224,15 @@ int main(int argc, char** argv) {
     CALL(im_destroy)(p);
     return 0;
   }
+  if (what == "growing_reads") {   // one env, two, ... of a pool
+    const Shape s{200, 4, 2, 64, 2, 64, 2, IM_F32, 1};
+    im_pool* p = make(s);
+    g_log = true;
+    for (int n = 1; n <= s.E; ++n) read_and_write(p, s, 0, n, false);
+    g_log = false;
+    CALL(im_destroy)(p);
+    return 0;
+  }
   printf("no scenario %s\n", what.c_str());
   return 2;
 }

@@ -85,3 +85,10 @@ def test_chain_grid_covers_every_row_count(program, E, M, slots, n, hidden, cus)
         assert pairs + singles <= grid
         assert 32 * pairs + 16 * singles >= rows and 32 * pairs <= rows + 31
     assert grid <= max(cus * -(-bound // (32 * cus)), -(-bound // 16))
+
+
+def test_growing_reads_allocate_seldom(program):
+    """200 reads, each of one env more than the last: the staging grows by doubling."""
+    text = run(program, "growing_reads")
+    assert sum("export_kernel" in k for k, *_ in launches(text)) >= 200
+    assert 1 <= text.count("host memory") <= 9, text.count("host memory")   # 1 env to 200: less than 2^8
