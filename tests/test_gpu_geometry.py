@@ -3,16 +3,17 @@ the bf16 route kernels gather.
 
 * Launch shapes (im_set_launch): the same pool state ticked with the default
   persistent route grid (one block per compute unit), grids of 37 and of 1
-  block, and the kernels that launch one wave per row tile, with 4, 2 and 1
-  envs per schedule workgroup. Actions, logits and the whole integer state are
-  identical bit for bit across the persistent grids and workgroup sizes; the
-  one-wave-per-tile kernels agree with them within the logit tolerance (and
-  the integer state is compared where no near tie flipped an action).
+  block, and the kernels that launch one block per group of rows, with 4, 2
+  and 1 envs per schedule workgroup. Actions, logits and the whole integer
+  state are identical bit for bit across the persistent grids and workgroup
+  sizes; the block-per-group kernels agree with them within the logit tolerance
+  (and the integer state is compared where no near tie flipped an action).
 * Feature columns: a policy whose layers are 0/1 selections (layer 1 picks one
   input column per hidden unit, deeper layers pass it on, the output layer
   reads it out) turns each logit into one feature, rounded to bf16 (twice,
   which is once). Every load-statistic column and the budget column of the
-  c2, c3 and c4 shapes is read this way through the benchmark's kernels and
+  c2, c3 and c4 shapes is read this way through the kernels of small ticks (the
+  default grid) and, on a grid of one block, through the persistent kernels and
   compared bit for bit with the oracle's feature vector (Eq. 1 restated): a
   swapped, shifted or mis-scaled column fails, which the 2e-2 logit tolerance
   of the lockstep tests could hide."""
@@ -66,7 +67,7 @@ def test_launch_shapes_identical(name, over):
                 np.testing.assert_array_equal(lgs[t], ref[1][t], err_msg=f"logits grid {rb} t={t}")
             assert_state_equal(s, ref[2], ctx=f"grid {rb} waves {sw}")
             continue
-        # one wave per row tile: the same arithmetic per row, so the same
+        # one block per group of rows: the same arithmetic per row, so the same
         # bits are expected; the tolerance is the contract
         flips, bitwise = 0, True
         for t in range(cfg["T"]):
@@ -76,9 +77,9 @@ def test_launch_shapes_identical(name, over):
             for r in np.nonzero(acts[t] != ref[0][t])[0]:
                 assert near_tie(b[r], int(ref[0][t][r]), int(acts[t][r]), rtol), (t, r)
                 flips += 1
-        note(f"  one-wave-per-tile kernels: logits bitwise equal {bitwise}, flips {flips}")
+        note(f"  block-per-group kernels: logits bitwise equal {bitwise}, flips {flips}")
         if flips == 0:
-            assert_state_equal(s, ref[2], ctx="one wave per tile")
+            assert_state_equal(s, ref[2], ctx="a block per group")
 
 
 def _select_weights(cfg, cols):
@@ -97,11 +98,14 @@ def _select_weights(cfg, cols):
     return W, b
 
 
-SHAPES = [("c2", dict(E=6, lam=24.0)), ("c4", dict(E=6, lam=40.0)), ("c3", dict(E=4, lam=24.0))]
+# grid 1: ticks of about 96 (very light shape), 144 (light), 480 rows (64-row tiles) on c2's persistent kernels
+SHAPES = [("c2", dict(E=6, lam=24.0), -1), ("c4", dict(E=6, lam=40.0), -1), ("c3", dict(E=4, lam=24.0), -1),
+          ("c2", dict(E=4, lam=24.0), 1), ("c2", dict(E=6, lam=24.0), 1), ("c2", dict(E=20, lam=24.0), 1),
+          ("c4", dict(E=6, lam=40.0), 1), ("c3", dict(E=8, lam=24.0), 1)]
 
 
-@pytest.mark.parametrize("name,over", SHAPES, ids=[s[0] for s in SHAPES])
-def test_feature_columns_exact(name, over):
+@pytest.mark.parametrize("name,over,blocks", SHAPES, ids=[f"{s[0]}-{s[1]['E']}-{s[2]}" for s in SHAPES])
+def test_feature_columns_exact(name, over, blocks):
     torch = need_gpu()
     import paper_2606_11440_amd as P
     cfg = workload.configs.get(name, T=14, **over)
@@ -118,6 +122,7 @@ def test_feature_columns_exact(name, over):
         cols = tail[c0:c0 + A]
         W, b = _select_weights(cfg, cols)
         gpu = P.Pool(cfg, W, b, emb_dev, cap, None)
+        gpu.set_launch(blocks)
         orc = oracle.Oracle(cfg, W, b, emb_vals, cap, None, E=cfg["E"], threads=4)
         for t in range(cfg["T"]):
             arr = workload.gen.tick(cfg, 61, t, counts[t], Q)
