@@ -304,12 +304,15 @@ bool split_supported(int hidden) {
 // tile. Past that the wide layers (hidden 256, 512) take 128 rows and two
 // feature tiles per wave, which halves the weight bytes from L2 and the
 // activation bytes from LDS per MFMA; the narrow ones, whose weights stay in
-// the vector cache, keep 64 rows (more blocks per compute unit). us per launch at
-// 32 / 64 / 128 rows per block, greedy:
-//   405 -> 256 -> 256 -> 15  8,192 rows 11.4 / 13.5 / 18.4, 16,384 rows 16.9 / 14.7 / 19.3,
-//                            131,072 rows 111 / 78 / 64
-//   97 -> 128 -> 128 -> 32   8,192 rows 6.1 / 6.7 / 11.1, 131,072 rows 29.7 / 21.9 / 20.2
-//   85 -> 64 -> 15           8,192 rows 5.0 / 5.2 / 11.7, 131,072 rows 14.9 / 11.5 / 17.5
+// the vector cache, keep 64 rows (more blocks per compute unit): at hidden 128
+// the 128-row shape is ahead in a band around 131,072 rows only. us per launch at
+// 32 / 64 / 128 rows per block, greedy (128 rows of the narrow shapes: compiled for
+// the comparison):
+//   405 -> 256 -> 256 -> 15  8,192 rows 10.0 / 12.2 / 17.2, 16,384 rows 14.5 / 12.5 / 17.3,
+//                            65,536 rows 50.8 / 36.0 / 30.6, 131,072 rows 97.6 / 68.1 / 57.3
+//   97 -> 128 -> 128 -> 32   8,192 rows 5.2 / 6.0 / 10.3, 65,536 rows 14.4 / 10.5 / 12.6,
+//                            131,072 rows 25.9 / 18.4 / 16.3, 262,144 rows 53.7 / 35.1 / 37.6
+//   85 -> 64 -> 15           8,192 rows 4.5 / 4.9 / 10.6, 131,072 rows 12.4 / 9.4 / 13.5
 // bias_last: the shape has no persistent kernel.
 hipError_t launch_split(const RouteArgs& a, int hidden, int n_layers, int out_tiles, bool bias_last, hipStream_t s) {
   const int64_t cus = a.persistent_blocks > 0 ? a.persistent_blocks : a.cus;

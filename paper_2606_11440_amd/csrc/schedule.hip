@@ -332,12 +332,6 @@ __global__ void snapshot_kernel(SchedArgs a, int e0, int ne) {
   }
 }
 
-__device__ __forceinline__ int32_t wave_sum32(int32_t v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += shfl_xor(v, m);
-  return v;
-}
-
 constexpr int kStageChunks = 4;   // arrival chunks (of 64) staged in LDS per round
 
 // Per-model state of the env, one model per lane (lane m: model m) in

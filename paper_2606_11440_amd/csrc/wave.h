@@ -1,7 +1,7 @@
 // Wavefront primitives for gfx950 (64-lane waves).
 //
 // Ballot / prefix counts (mbcnt), cross-lane exchanges, a 64-lane bitonic
-// sort network on 32- or 64-bit keys, and fp32 -> bf16 round-to-nearest-even.
+// sort network on 32- or 64-bit keys, and bf16 -> fp32.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -42,12 +42,6 @@ __device__ __forceinline__ int64_t shfl(int64_t v, int src) {
   int32_t hi = __shfl((int32_t)(v >> 32), src, kWave);
   return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
-// Value of a 64-bit variable in lane `src` (wave-uniform result).
-__device__ __forceinline__ int64_t readlane64(int64_t v, int src) {
-  const uint32_t lo = __builtin_amdgcn_readlane((int32_t)(uint32_t)v, src);
-  const uint32_t hi = __builtin_amdgcn_readlane((int32_t)(v >> 32), src);
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 __device__ __forceinline__ int32_t shfl_xor(int32_t v, int m) { return __shfl_xor(v, m, kWave); }
 __device__ __forceinline__ int64_t shfl_xor(int64_t v, int m) {
   int32_t lo = __shfl_xor((int32_t)(uint32_t)v, m, kWave);
@@ -55,12 +49,7 @@ __device__ __forceinline__ int64_t shfl_xor(int64_t v, int m) {
   return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// Wave-wide sums (every lane gets the result).
-__device__ __forceinline__ int64_t wave_sum(int64_t v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += shfl_xor(v, m);
-  return v;
-}
+// Wave-wide OR (every lane gets the result).
 __device__ __forceinline__ uint64_t wave_or(uint64_t v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v |= (uint64_t)shfl_xor((int64_t)v, m);
@@ -230,24 +219,11 @@ __device__ __forceinline__ void bitonic_sort_first(KT& k, int n) {
   bitonic_block<64, 1>(k, none);
 }
 
-// Key-only variants (no payload).
+// Key-only variant (no payload).
 template <typename KT>
 __device__ __forceinline__ void bitonic_sort64(KT& k) {
   int32_t none[1] = {0};   // dead after the network; removed by the compiler
   bitonic_sort64<1>(k, none);
-}
-template <typename KT>
-__device__ __forceinline__ void bitonic_merge64(KT& k) {
-  int32_t none[1] = {0};
-  bitonic_merge64<1>(k, none);
-}
-
-// fp32 -> bf16 bits, round to nearest even (NaN kept quiet).
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
 }
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {

@@ -6,8 +6,9 @@ Eight service slots per model with base service 1 tick start ~4 requests per
 model and tick. With arrival-order keys (FCFS), a newcomer is never below the
 front's largest key, so the front only shrinks by pops and every 64 pops are
 followed by a refill from the whole pool (growing by ~9 entries per tick
-until the queue fills); with slack keys the pool order is random, so the scan
-keeps collecting candidates below its running threshold and merges them.
+until the queue fills); with slack keys the pool order is random. Pools of up to
+256 entries are sorted whole, longer ones scanned for the keys below a threshold
+sampled from the pool.
 Lockstep with the oracle, integer state bit-exact (the queue contents in
 order, the slots, the counters), single-step and chain pools."""
 import pytest

@@ -1,7 +1,7 @@
 """GPU parity on policy shapes outside the five workloads, so that every
 route kernel variant runs: fp32 with one wave per 16-row tile (hidden width 32)
 and feature-split (hidden widths in tile quads), fp32 and bf16 with several
-output tiles, and the generic (non-persistent) bf16 kernel. Lockstep with the
+output tiles, and bf16 shapes without a persistent kernel. Lockstep with the
 oracle as in the workload tests (logits within 1e-4 fp32 / 2e-2 bf16 of the
 row's largest oracle logit, actions equal except at near ties, integer state
 bit-exact), greedy route and schedule, then RL outputs with a value head."""
