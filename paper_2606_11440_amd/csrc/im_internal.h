@@ -134,6 +134,7 @@ struct RouteArgs {
   float* value;                       // row A of the last layer (value head), or NULL
   const int32_t* n_total_dev;         // chain pools: the tick's row count (device); n_total
                                       // then bounds it
+  int32_t n_least;                    // rows the tick has at least (chain pools: its arrivals; else n_total)
   // dual-pathway executor (net == IM_NET_DUAL): W[0] semantic (query half),
   // W[1] merge, W[2] action/value fragments; W_res resource-layer fragments
   int32_t net;

@@ -1404,7 +1404,11 @@ hipError_t launch_route(const RouteArgs& a, int dtype, int hidden, int n_layers,
     // blocks) runs the 16-wave, 32-row shape: twice the waves share its rows;
     // a very light one (at most one 32-row tile per two waves) runs 8 waves
     // of 32 rows whose first tile's loads overlap the block's weight copy
-    const int64_t rows = a.n_total, cap = (int64_t)64 * 8 * a.persistent_blocks;
+    // Chain pools, whose rows are not known here: greedy ticks go by the bound, RL
+    // outputs by the arrivals, so that few rows under a large bound are not spread
+    // over 64-row tiles (us per im_route_sample, 86 -> 256 -> 256 -> 16, by the bound
+    // / by the arrivals, 22,551 rows of at most 180,224, 25.6 / 23.5).
+    const int64_t rows = a.rl ? a.n_least : a.n_total, cap = (int64_t)64 * 8 * a.persistent_blocks;
     const int light = rows * 4 <= cap ? 2 : (rows * 4 <= 3 * cap ? 1 : 0);
     const LdsLaunch kl = pick_lds(dtype, hidden, n_layers, out_tiles, a.k1, a.embed_dim, a.rl != 0, light,
                                   rows / a.persistent_blocks);

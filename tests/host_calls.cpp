@@ -112,11 +112,12 @@ static int need(im_status s, const char* what) {
 
 struct Shape {
   int E, M, K, qcap, slots, hidden, layers, dtype, steps;
+  int embed = 32;
 };
 static im_pool* make(const Shape& s) {
   im_pool_desc d{};
   d.n_envs = s.E; d.n_models = s.M; d.n_depths = s.K; d.queue_cap = s.qcap; d.max_slots = s.slots;
-  d.embed_dim = 32; d.feat_dim = 32 + 4 * s.M + 1; d.n_layers = s.layers;
+  d.embed_dim = s.embed; d.feat_dim = s.embed + 4 * s.M + 1; d.n_layers = s.layers;
   for (int l = 0; l + 1 < s.layers; ++l) d.widths[l] = s.hidden;
   d.widths[s.layers - 1] = s.M * s.K;
   d.dtype = s.dtype; d.max_arrivals_per_env_tick = 1 << 16; d.budget_max = 100; d.max_steps = s.steps;
@@ -229,6 +230,22 @@ int main(int argc, char** argv) {
     im_pool* p = make(s);
     g_log = true;
     for (int n = 1; n <= s.E; ++n) read_and_write(p, s, 0, n, false);
+    g_log = false;
+    CALL(im_destroy)(p);
+    return 0;
+  }
+  if (what == "chain_rl") {   // models slots arrivals layers
+    const int E = 64, n = atoi(argv[5]);
+    g_cus = 8;
+    Shape s{E, atoi(argv[3]), 3, 1, atoi(argv[4]), 256, atoi(argv[6]), IM_BF16, 3};
+    s.embed = 64;
+    im_pool* p = make(s);
+    std::vector<int32_t> act((size_t)n + E * s.M * s.slots);
+    const im_arrivals a = arrivals(n, E);
+    im_policy_out o{};
+    o.actions = act.data();
+    g_log = true;
+    need(CALL(im_route_sample)(p, &a, 1, 0, &o, nullptr), "im_route_sample");
     g_log = false;
     CALL(im_destroy)(p);
     return 0;

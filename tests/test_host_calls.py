@@ -92,3 +92,16 @@ def test_growing_reads_allocate_seldom(program):
     text = run(program, "growing_reads")
     assert sum("export_kernel" in k for k, *_ in launches(text)) >= 200
     assert 1 <= text.count("host memory") <= 9, text.count("host memory")   # 1 env to 200: less than 2^8
+
+
+@pytest.mark.parametrize("M,slots,n,layers,tile", [(5, 8, 200, 3, 32), (5, 8, 4000, 3, 64), (8, 8, 5000, 2, 32),
+                                                   (8, 8, 9000, 2, 64)])
+def test_chain_rl_rows_per_tile(program, M, slots, n, layers, tile):
+    """RL outputs of a chain pool run 64-row wave tiles when its arrivals alone are
+    a heavy tick (8 compute units: above 3,072 rows for the three-layer shape, from
+    8,192 rows on for the two-layer one), whatever the bound on its rows is."""
+    text = run(program, "chain_rl", *map(str, (M, slots, n, layers)))
+    kernel = next(k for k, *_ in launches(text) if "route_bf16_lds" in k)
+    args = re.search(r"route_bf16_ldsI(.*)EEvNS", kernel).group(1)   # H, layers, output tiles, K blocks, LDS, waves, ED, row tiles, ...
+    row_tiles = int(re.findall(r"L[ib](\d+)E", args + "E")[7])
+    assert 32 * row_tiles == tile, kernel
