@@ -303,3 +303,45 @@ def test_chain_pool_refuses_missing_n_steps_and_write_state():
         p.gpu.write_state(0, s)
     assert ei.value.status == P._lib.IM_EUNSUPPORTED
     p.close()
+
+
+@pytest.mark.parametrize("E", [4096, 4097, 9001])
+def test_chain_rows_of_many_envs(E):
+    """The rows of pools of more envs than one pass of the scan takes (4,096): the
+    row offsets count every env's pending calls and arrivals, and every row is
+    routed; a break of the CSR behind the first pass skips the whole tick."""
+    torch = need_gpu()
+    import paper_2606_11440_amd as P
+    cfg = workload.configs.get("c2c", E=E, T=6, lam=1.5, M=2, K=1, qcap=16, svc_mu=0.0, embed_dim=32, feat_dim=41,
+                               widths=[32, 2])
+    note(f"[chain_many_envs] E={E}")
+    W, b = workload.gen.weights(cfg, 5, 0.1)
+    pool = P.Pool(cfg, W, b, torch.zeros((64, 32), dtype=torch.bfloat16, device="cuda"), workload.gen.capacities(cfg, 5))
+    counts = workload.gen.counts(cfg, 5)
+    for t in range(cfg["T"]):
+        arr = workload.gen.tick(cfg, 5, t, counts[t], 64)
+        c = pool.chain_state()
+        n = arr["q_idx"].size
+        act = torch.full((n + E * 2 * cfg["max_slots"],), -7, dtype=torch.int32, device="cuda")
+        dev = P.device_arrivals(arr)
+        pool.route(dev, act)
+        off, n_rows = pool.rows()
+        pend = np.asarray(c["pending_count"])
+        want = np.concatenate([[0], np.cumsum(pend + np.diff(arr["offsets"]))])
+        np.testing.assert_array_equal(off, want, err_msg=f"t={t}")
+        assert n_rows == want[-1]
+        a = act.cpu().numpy()
+        assert (a[:want[-1]] >= -1).all() and (a[want[-1]:] == -7).all()
+        pool.schedule(dev, act)
+        assert int(pool.state(with_queues=False)["arrived"].sum()) >= n
+    assert pend.sum() > 0 and pool.error() == 0
+    s = pool.state()
+    arr = workload.gen.tick(cfg, 5, 0, counts[0], 64)
+    arr["offsets"][E - 1] += 3 + arr["offsets"][E] - arr["offsets"][E - 1]   # past the next env's start
+    act = torch.full((arr["q_idx"].size + E * 2 * cfg["max_slots"],), -7, dtype=torch.int32, device="cuda")
+    pool.tick(P.device_arrivals(arr), act)
+    assert pool.error() == 2
+    g = pool.state()
+    for k in ("arrived", "completed", "qlen", "next_id"):
+        np.testing.assert_array_equal(g[k], s[k], err_msg=k)
+    pool.close()
