@@ -131,10 +131,16 @@ __device__ __forceinline__ void merge_front(Queue& q, int4& fe, int2& fx, const 
   if constexpr (CHAIN) fx = lane < keep ? make_int2(plo[1], plo[2]) : make_int2(0, 0);
 }
 
-// Chunks of 64 pool keys a refill has in flight, and the candidates its LDS
-// list has room for.
-constexpr int kScanChunks = 8;
-constexpr int kCandidates = 1024;
+// Chunks of 64 pool keys that a refill has in flight, by the queues' capacity (LONG:
+// above kLongQueue). Long queues want the deeper scan, whose registers the wave's
+// per-model state has to leave (it waits in LDS); short ones lose more by that
+// than they gain. schedule_kernel in us, 4,096 envs of 40 requests, 8 slots, slack
+// keys, short / long: queues of 256 19.6 / 20.7, 512 20.7 / 21.0, 768 22.9 / 23.7;
+// of 64 requests, queues of 1,024 25.8 / 25.5, 2,048 (3 slots) 26.4 / 25.4.
+constexpr int kLongQueue = 768;
+template <bool LONG>
+constexpr int scan_chunks() { return LONG ? 8 : 4; }
+constexpr int kCandidates = 1024;   // room of the LDS list of candidates
 
 // Refill the (empty) front with the min(64, P) smallest pool entries; the new
 // front is returned in `fe` (lane i: entry i), the front array is not written.
@@ -144,15 +150,21 @@ constexpr int kCandidates = 1024;
 // A launch lasts as long as its slowest envs, which are those that refill, so
 // one wave's latency counts. Sixty-four keys sampled across the pool give a
 // threshold that about 190 of 2,000 keys do not exceed; a scan of the keys alone
-// (registers, 8 chunks in flight) lists those, and only they are sorted, 64 at a
-// time; a pool of up to 256 entries is sorted whole. Merging every candidate
-// below a running threshold that started at the first chunk's maximum, over LDS
-// copies of keys and ids, took five sorts and eight rounds (9 us of scanning a
-// refill, now 4). schedule_kernel with queues of 2,048 full, 4,096 envs of 64
-// requests: 30.8 -> 25.2 us; chains 29.5 -> 24.4; queues of 256: 21.9 -> 22.4.
-template <bool CHAIN>
+// lists those, and only they are sorted, 64 at a time; a short pool is sorted
+// whole. A batch none of whose entries is below the largest of the best 64 is
+// passed over: arrival-order keys lie about in order in the pool, and its first
+// batch is often all there is to sort (which is why such pools are sorted whole up
+// to 256 entries in short queues too). Merging every candidate below a running
+// threshold that started at the first chunk's maximum, over LDS copies of keys and
+// ids, took five sorts and eight rounds on a long pool of random keys (9 us of
+// scanning a refill, now 4).
+// schedule_kernel in us, that / this: queues of 2,048 full, 4,096 envs of 64
+// requests, 28.4 / 24.1; of 256, 8 slots, 20.0 / 19.7, arrival-order keys 18.0 / 17.7;
+// of 1,024 30.1 / 25.5, arrival-order keys 23.8 / 21.9.
+template <bool CHAIN, bool LONG>
 __device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext, int32_t* cand, int key_mode) {
   const int lane = lane_id();
+  constexpr int NC = scan_chunks<LONG>();
   const int P = q.P;
   wave_mem_sync();   // this tick's pool appends are read below
   if (P <= kFront) {
@@ -189,6 +201,7 @@ __device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext,
   // and taken elementwise-min with the best set it gives a bitonic sequence
   // holding the 64 smallest of both, which one merge network sorts.
   auto merge_batch = [&](int64_t bk, int32_t (&bi)[1]) {
+    if (some && ballot(bk < readlane64(ck, 63)) == 0) return;
     bitonic_sort64<1>(bk, bi);
     if (!some) {
       ck = bk;
@@ -206,18 +219,18 @@ __device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext,
   auto at = [&](uint32_t i) { return reinterpret_cast<const char*>(pool) + i * 16u; };
   auto key_at = [&](uint32_t i) { return *reinterpret_cast<const int32_t*>(at(i)); };
   auto entry_at = [&](uint32_t i) { return *reinterpret_cast<const int2*>(at(i)); };
-  if (P <= 256) {
+  if (P <= (LONG || key_mode == IM_KEY_FCFS ? 256 : 128)) {
     // every entry is a candidate (a threshold would save at most two sorts): all in flight at once
-    int2 e[4];
+    constexpr int W = 4;
+    int2 e[W];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) e[c] = entry_at((uint32_t)min(c * 64 + lane, P - 1));
+    for (int c = 0; c < W; ++c) e[c] = entry_at((uint32_t)min(c * 64 + lane, P - 1));
 #pragma unroll 1
     for (int b = 0; b < P; b += 64) {
       int32_t bi[1] = {b + lane};
       merge_batch(b + lane < P ? composite(e[0].x, e[0].y) : kKeyMax, bi);
-      e[0] = e[1];
-      e[1] = e[2];
-      e[2] = e[3];
+#pragma unroll
+      for (int c = 0; c + 1 < W; ++c) e[c] = e[c + 1];
     }
   } else {
     // The sample: entry l P / 64 in lane l (the pool keeps arrival order in
@@ -225,27 +238,27 @@ __device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext,
     // at or below its j-th smallest; j is chosen so that fewer than 64 do about
     // once in 20 refills, and the next threshold is then tried on the rest.
     int32_t sk = key_at(((uint32_t)lane * (uint32_t)P) >> 6);
-    int32_t kc[kScanChunks];   // a chunk's keys per register; lanes past the pool's end read its last entry
+    int32_t kc[NC];   // a chunk's keys per register; lanes past the pool's end read its last entry
 #pragma unroll
-    for (int c = 0; c < kScanChunks; ++c) kc[c] = key_at((uint32_t)min(c * 64 + lane, P - 1));
+    for (int c = 0; c < NC; ++c) kc[c] = key_at((uint32_t)min(c * 64 + lane, P - 1));
     bitonic_sort64(sk);
     int32_t below = (int32_t)0x80000000;   // keys at or below it are already merged (no key is the lowest int)
     int np = 0, found = 0;                 // candidates listed, and in all
     for (int j = 5120 / P + 3; found < kFront; j = 2 * j + 4) {
       const int32_t thr = j < 63 ? __builtin_amdgcn_readlane(sk, j) : 0x7fffffff;
-      for (int c0 = 0; c0 * 64 < P; c0 += kScanChunks) {
+      for (int c0 = 0; c0 * 64 < P; c0 += NC) {
 #pragma unroll
-        for (int c = 0; c < kScanChunks; ++c) {
+        for (int c = 0; c < NC; ++c) {
           const int i = (c0 + c) * 64 + lane;
           const uint64_t cm = ballot(kc[c] <= thr && kc[c] > below && i < P);
-          kc[c] = key_at((uint32_t)min(i + kScanChunks * 64, P - 1));
+          kc[c] = key_at((uint32_t)min(i + NC * 64, P - 1));
           if (cm != 0) {
             if ((cm >> lane) & 1ull) cand[np + prefix_count(cm)] = i;
             np += popc64(cm);
           }
         }
         // merge them at the pass's end, or when the next chunks might not fit the list
-        if (np > kCandidates - kScanChunks * 64 || (c0 + kScanChunks) * 64 >= P) {
+        if (np > kCandidates - NC * 64 || (c0 + NC) * 64 >= P) {
           found += np;
           for (int b = 0; b < np; b += 64) {
             const bool on = b + lane < np;
@@ -259,7 +272,7 @@ __device__ void refill(Queue& q, int4& fe, int2& fx, int4* pool, int2* pool_ext,
       below = thr;
       if (found < kFront) {
 #pragma unroll
-        for (int c = 0; c < kScanChunks; ++c) kc[c] = key_at((uint32_t)min(c * 64 + lane, P - 1));
+        for (int c = 0; c < NC; ++c) kc[c] = key_at((uint32_t)min(c * 64 + lane, P - 1));
       }
     }
   }
@@ -405,7 +418,7 @@ __device__ __forceinline__ void counter_add(int64_t* p, int64_t v) {
 // call carries its query's two chain words through the queue, and a
 // completion that is not its query's last call appends the next call, with
 // the query's deadline, to the pending list of the next tick.
-template <bool RPM, bool CHAIN, int PF>
+template <bool RPM, bool CHAIN, int PF, bool LONG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void schedule_kernel(SchedArgs a) {
   // sorted chunks; in the service phase the refill's candidate list, then the
   // counter staging
@@ -414,7 +427,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   __shared__ int32_t hist_lds[4][IM_MAX_ACTIONS];
   __shared__ int32_t mw_lds[4][MW_NUM][IM_MAX_MODELS];
   __shared__ unsigned long long md_lds[4][MD_NUM][IM_MAX_MODELS];
-  __shared__ int32_t park[4][PK_NUM][IM_MAX_MODELS];
+  __shared__ int32_t park[LONG ? 4 : 1][PK_NUM][IM_MAX_MODELS];
   static_assert(sizeof(int4) * kStageChunks * 64 >= sizeof(int32_t) * kCandidates, "the candidate list fits the stage");
   static_assert(kStageChunks * 64 >= (C_NUM / 2) * IM_MAX_MODELS, "the counter staging fits the stage");
   static_assert(IM_MAX_MODELS < 63, "model 63 marks rows not admitted");
@@ -926,10 +939,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     uint64_t dry = ballot(npop_l > L.fn);
     if (dry != 0) {
       if (dry & wrote) wave_mem_sync();
-      // The per-model state waits in LDS meanwhile: the refill needs the
+      // LONG: the per-model state waits in LDS meanwhile: the refill needs the
       // registers for the pool's keys.
-      int32_t(*pk)[IM_MAX_MODELS] = park[wv];
-      if (lane < IM_MAX_MODELS) {
+      int32_t(*pk)[IM_MAX_MODELS] = park[LONG ? wv : 0];
+      if (LONG && lane < IM_MAX_MODELS) {
         pk[PK_QLEN][lane] = L.qlen; pk[PK_BUSY][lane] = L.busy; pk[PK_EWMA][lane] = L.ewma;
         pk[PK_BACKLOG][lane] = L.backlog; pk[PK_FH][lane] = L.fh; pk[PK_FN][lane] = L.fn;
         pk[PK_P][lane] = L.P; pk[PK_MASK][lane] = L.busy_mask; pk[PK_DONE][lane] = L.next_done;
@@ -940,16 +953,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
         const int m = __builtin_ctzll(dry);
         dry &= dry - 1;
         const size_t em = em0 + m;
-        const int ofh = __builtin_amdgcn_readfirstlane(pk[PK_FH][m]), ofn = __builtin_amdgcn_readfirstlane(pk[PK_FN][m]);
+        auto state = [&](int row, int32_t v) {
+          return LONG ? __builtin_amdgcn_readfirstlane(pk[row][m]) : rl(v, m);
+        };
+        const int ofh = state(PK_FH, L.fh), ofn = state(PK_FN, L.fn);
         Queue q;
-        q.P = __builtin_amdgcn_readfirstlane(pk[PK_P][m]);
+        q.P = state(PK_P, L.P);
         q.fh = 0;
         q.fn = 0;
         int4 fe;
         int2 fx;
         int4* pool = a.pool + em * a.qcap;
         int2* pool_x = CHAIN ? a.pool_ext + em * a.qcap : nullptr;
-        refill<CHAIN>(q, fe, fx, pool, pool_x, reinterpret_cast<int32_t*>(st), a.key_mode);
+        refill<CHAIN, LONG>(q, fe, fx, pool, pool_x, reinterpret_cast<int32_t*>(st), a.key_mode);
         int4 old = make_int4(0, 0, 0, 0);
         int2 oldx = make_int2(0, 0);
         if (lane < ofn) {
@@ -976,24 +992,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
           a.front[em * kFront + lane] = ne;
           if constexpr (CHAIN) a.front_ext[em * kFront + lane] = nx;
         }
-        if (lane == nf - 1) {
-          pk[PK_P][m] = q.P;
-          pk[PK_FH][m] = 0;
-          pk[PK_FN][m] = nf;
-          pk[PK_FMK][m] = ne.x;
-          pk[PK_FMI][m] = ne.y;
-          pk[PK_CHG][m] |= CH_FRONT | CH_POOL;
+        if constexpr (LONG) {
+          if (lane == nf - 1) {
+            pk[PK_P][m] = q.P;
+            pk[PK_FH][m] = 0;
+            pk[PK_FN][m] = nf;
+            pk[PK_FMK][m] = ne.x;
+            pk[PK_FMI][m] = ne.y;
+            pk[PK_CHG][m] |= CH_FRONT | CH_POOL;
+          }
+        } else {
+          const int32_t nk = rl(ne.x, nf - 1), ni = rl(ne.y, nf - 1);
+          if (lane == m) {
+            L.P = q.P;
+            L.fh = 0;
+            L.fn = nf;
+            L.fmk = nk;
+            L.fmi = ni;
+            L.chg |= CH_FRONT | CH_POOL;
+          }
         }
         wrote |= 1ull << m;
       }
       asm volatile("" ::: "memory");
-      if (lane < IM_MAX_MODELS) {   // the other lanes hold no model
-        L.qlen = pk[PK_QLEN][lane]; L.busy = pk[PK_BUSY][lane]; L.ewma = pk[PK_EWMA][lane];
-        L.backlog = pk[PK_BACKLOG][lane]; L.fh = pk[PK_FH][lane]; L.fn = pk[PK_FN][lane];
-        L.P = pk[PK_P][lane]; L.busy_mask = pk[PK_MASK][lane]; L.next_done = pk[PK_DONE][lane];
-        L.fmk = pk[PK_FMK][lane]; L.fmi = pk[PK_FMI][lane]; L.chg = pk[PK_CHG][lane];
-      } else {
-        L = LaneState{};
+      if constexpr (LONG) {
+        if (lane < IM_MAX_MODELS) {   // the other lanes hold no model
+          L.qlen = pk[PK_QLEN][lane]; L.busy = pk[PK_BUSY][lane]; L.ewma = pk[PK_EWMA][lane];
+          L.backlog = pk[PK_BACKLOG][lane]; L.fh = pk[PK_FH][lane]; L.fn = pk[PK_FN][lane];
+          L.P = pk[PK_P][lane]; L.busy_mask = pk[PK_MASK][lane]; L.next_done = pk[PK_DONE][lane];
+          L.fmk = pk[PK_FMK][lane]; L.fmi = pk[PK_FMI][lane]; L.chg = pk[PK_CHG][lane];
+        } else {
+          L = LaneState{};
+        }
       }
       wave_mem_sync();
     }
@@ -1279,6 +1309,13 @@ __global__ __launch_bounds__(256) void dual_recount_kernel(SchedArgs a, bool cha
   a.dual_shards[2 * i + 1] = part[1][0] + part[1][1] + part[1][2] + part[1][3];
 }
 
+typedef void (*ScheduleKernel)(SchedArgs);
+template <bool LONG>
+ScheduleKernel pick_schedule(bool rpm, bool chain) {
+  if (chain) return rpm ? schedule_kernel<true, true, 1, LONG> : schedule_kernel<false, true, 1, LONG>;
+  return rpm ? schedule_kernel<true, false, 2, LONG> : schedule_kernel<false, false, 2, LONG>;
+}
+
 }  // namespace
 
 hipError_t launch_dual_update(const int64_t* shards, int64_t* last, double eta, double lambda_max, double* lambda,
@@ -1307,13 +1344,8 @@ hipError_t launch_schedule(const SchedArgs& a, bool rpm, bool chain, int waves_p
   const int w = waves_per_block == 1 || waves_per_block == 2 ? waves_per_block : 4;
   const unsigned blocks = (unsigned)(((int64_t)a.E + w - 1) / w);
   const dim3 threads(64 * w);
-  if (chain) {
-    if (rpm) hipLaunchKernelGGL((schedule_kernel<true, true, 1>), dim3(blocks), threads, 0, s, a);
-    else hipLaunchKernelGGL((schedule_kernel<false, true, 1>), dim3(blocks), threads, 0, s, a);
-  } else {
-    if (rpm) hipLaunchKernelGGL((schedule_kernel<true, false, 2>), dim3(blocks), threads, 0, s, a);
-    else hipLaunchKernelGGL((schedule_kernel<false, false, 2>), dim3(blocks), threads, 0, s, a);
-  }
+  ScheduleKernel k = a.qcap > kLongQueue ? pick_schedule<true>(rpm, chain) : pick_schedule<false>(rpm, chain);
+  hipLaunchKernelGGL(k, dim3(blocks), threads, 0, s, a);
   return hipGetLastError();
 }
 

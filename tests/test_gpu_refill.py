@@ -6,9 +6,9 @@ Eight service slots per model with base service 1 tick start ~4 requests per
 model and tick. With arrival-order keys (FCFS), a newcomer is never below the
 front's largest key, so the front only shrinks by pops and every 64 pops are
 followed by a refill from the whole pool (growing by ~9 entries per tick
-until the queue fills); with slack keys the pool order is random. Pools of up to
-256 entries are sorted whole, longer ones scanned for the keys below a threshold
-sampled from the pool.
+until the queue fills); with slack keys the pool order is random. Short pools are
+sorted whole, longer ones scanned for the keys below a threshold sampled from the
+pool.
 Lockstep with the oracle, integer state bit-exact (the queue contents in
 order, the slots, the counters), single-step and chain pools."""
 import pytest
@@ -24,6 +24,15 @@ CASES = [
     ("slack_qcap1536", "c2", dict(FAST, qcap=1536, lam=64.0)),
     ("deadline_qcap384", "c2", dict(FAST, key_mode="deadline", qcap=384, lam=64.0)),
     ("chain_fcfs_qcap1024", "c2c", dict(FAST, key_mode="fcfs", qcap=1024, lam=24.0)),
+    # around the pool lengths that are sorted whole (128; 256 with arrival-order keys) and the capacity up to
+    # which the scan keeps four chunks in flight (768), not eight
+    ("slack_qcap200", "c2", dict(FAST, qcap=200, lam=64.0)),
+    ("fcfs_qcap200", "c2", dict(FAST, key_mode="fcfs", qcap=200, lam=64.0)),
+    ("slack_qcap322", "c2", dict(FAST, qcap=322, lam=64.0)),
+    ("fcfs_qcap322", "c2", dict(FAST, key_mode="fcfs", qcap=322, lam=64.0)),
+    ("deadline_qcap768", "c2", dict(FAST, key_mode="deadline", qcap=768, lam=64.0)),
+    ("slack_qcap769", "c2", dict(FAST, qcap=769, lam=64.0)),
+    ("chain_slack_qcap300", "c2c", dict(FAST, qcap=300, lam=24.0)),
 ]
 
 
