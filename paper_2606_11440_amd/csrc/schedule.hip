@@ -418,6 +418,8 @@ __device__ __forceinline__ void counter_add(int64_t* p, int64_t v) {
 // call carries its query's two chain words through the queue, and a
 // completion that is not its query's last call appends the next call, with
 // the query's deadline, to the pending list of the next tick.
+// PF: merging models whose fronts are loaded together. LONG: queues above
+// kLongQueue entries (the refill's scan).
 template <bool RPM, bool CHAIN, int PF, bool LONG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void schedule_kernel(SchedArgs a) {
   // sorted chunks; in the service phase the refill's candidate list, then the
